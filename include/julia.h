@@ -181,7 +181,11 @@ typedef struct {
  *                   frames only or FP64 frames only, blocks that test their
  *                   last iterate, the lanes found escaped being replayed
  *                   with the counted test at the next refill round (other
- *                   launches take counted blocks).
+ *                   launches take counted blocks).  Frames that equal their
+ *                   own 180-degree rotation (an even degree, a Julia image,
+ *                   a window about 0, rows about the middle) are computed by
+ *                   half: with tile_h even, a tile takes tile_h / 2 rows and
+ *                   stores each count at the opposite pixel too.
  *   bail            JR_KERNEL_HYBRID: 1..4096; JR_KERNEL_ROWS: 1..64 (other
  *                   kernels ignore it).
  *   handoff         JR_KERNEL_ROWS, 0..256: rows run in groups for FP32 and

@@ -32,7 +32,10 @@ struct alignas(16) DevFrame {
     int32_t degree;          // map Z^degree + C (2: the quadratic map)
     int32_t map;             // kMapPoly, or kMapRational: Z^degree + C + lambda / Z^degree
     int32_t index;           // the frame's position in the caller's list (progress counters)
-    int32_t reserved[2];
+    int32_t mirror;          // 1: the image is its own 180-degree rotation; rows
+                             // [row_begin, row_end) are computed and each count also
+                             // goes to pixel (height - 1 - row, width - 1 - column)
+    int32_t reserved;
 };
 static_assert(sizeof(DevFrame) == 144, "DevFrame layout");
 

@@ -253,6 +253,28 @@ bool absorbing(const jr_frame& f) {
     return m <= kAbsorbingC;
 }
 
+// An even map sends Z and -Z to the same point, with every rounding alike (each
+// product and sum of the first step sees both signs or neither, and
+// round-to-nearest is odd).  On a window about 0 the pixel centres of (i, j) and
+// (W - 1 - i, H - 1 - j) are exact negatives, so the image is its own 180-degree
+// rotation and half of its rows give the rest.  The rows must be a band about the
+// middle.  Only the rows kernel stores mirrored pixels, and a tile must hold an
+// even number of rows: it then takes half as many and their mirror images, so a
+// frame has as many tiles, each of as many pixels, as without.
+bool mirrors(const jr_frame& f, const jr_schedule& s) {
+    if (s.kernel != JR_KERNEL_ROWS || f.mode != JR_JULIA || (f.degree & 1)) return false;
+    if (0.5 * (f.w.re_min + f.w.re_max) != 0.0 || 0.5 * (f.w.im_min + f.w.im_max) != 0.0)
+        return false;
+    const int32_t rend = f.row_end == 0 ? f.height : f.row_end;
+    const int32_t rows = rend - f.row_begin;
+    return f.row_begin == f.height - rend && rows > 1 && (s.tile_h >= rows || s.tile_h % 2 == 0);
+}
+
+// frame_cost of the rows that a launch computes.
+double launch_cost(const jr_frame& f, const jr_schedule& s) {
+    return mirrors(f, s) ? 0.5 * frame_cost(f) : frame_cost(f);
+}
+
 // Totals of a frame table, for the launch shape and the kernel variant.
 struct TableStats {
     int64_t total_tiles = 0;
@@ -323,6 +345,11 @@ int64_t fill_frame(const jr_frame& f, const jr_schedule& s, int64_t tile_begin, 
     const int32_t th = s.kernel == JR_KERNEL_PLAIN ? 16 : s.tile_h;
     d.tile_w = std::min(tw, f.width);
     d.tile_h = std::min(th, d.row_end - d.row_begin);
+    if (mirrors(f, s)) {
+        d.mirror = 1;
+        d.row_end = d.row_begin + (d.row_end - d.row_begin + 1) / 2;
+        d.tile_h = (d.tile_h + 1) / 2;
+    }
     d.tiles_x = (f.width + d.tile_w - 1) / d.tile_w;
     const int64_t tiles_y = (d.row_end - d.row_begin + d.tile_h - 1) / d.tile_h;
     d.tile_begin = tile_begin;
@@ -336,16 +363,17 @@ void order_frames(const jr_frame* frames, int32_t n, const jr_schedule& s, int32
     std::iota(idx, idx + n, 0);
     if (s.order == JR_ORDER_COST)
         std::sort(idx, idx + n, [&](int32_t a, int32_t b) {
-            const double ca = frame_cost(frames[a]), cb = frame_cost(frames[b]);
+            const double ca = launch_cost(frames[a], s), cb = launch_cost(frames[b], s);
             return ca > cb || (ca == cb && a < b);
         });
 }
 
 // Adds a frame's tiles to the table totals.
-void account(TableStats& t, const jr_frame& f, const DevFrame& d, int64_t tiles) {
+void account(TableStats& t, const jr_frame& f, const jr_schedule& s, const DevFrame& d,
+             int64_t tiles) {
     t.total_tiles += tiles;
-    t.total_cost += frame_cost(f);
-    t.max_tile_cost = std::max(t.max_tile_cost, frame_cost(f) / (double)tiles);
+    t.total_cost += launch_cost(f, s);
+    t.max_tile_cost = std::max(t.max_tile_cost, launch_cost(f, s) / (double)tiles);
     t.dtmask |= 1 << f.dtype;
     if (d.degree > 2) t.dtmask |= jr::kGeneralBit;
     if (d.map == jr::kMapRational) t.dtmask |= jr::kGeneralBit | jr::kRationalBit;
@@ -354,9 +382,11 @@ void account(TableStats& t, const jr_frame& f, const DevFrame& d, int64_t tiles)
 // Launches holding rational frames run the rows kernel (or the plain kernel):
 // a schedule that asks for the tiled or hybrid stream is carried over to the
 // rows kernel with the same tiles, scheduling mode and refill threshold.
-void route_rational(const TableStats& t, jr_schedule& s) {
-    if (!(t.dtmask & jr::kRationalBit)) return;
+void route_rational(const jr_frame* frames, int32_t n, jr_schedule& s) {
     if (s.kernel != JR_KERNEL_TILED && s.kernel != JR_KERNEL_HYBRID) return;
+    if (std::none_of(frames, frames + n,
+                     [](const jr_frame& f) { return f.map == JR_MAP_RATIONAL; }))
+        return;
     s.kernel = JR_KERNEL_ROWS;
     s.unroll = s.unroll >= 8 ? 8 : 4;
     s.defer = 0;
@@ -374,7 +404,7 @@ void build_rows(const jr_frame* frames, int32_t n, const jr_schedule& s, DevFram
         const jr_frame& f = frames[idx[k]];
         const int64_t tiles = fill_frame(f, s, t.total_tiles, rows[k]);
         rows[k].index = idx[k];
-        account(t, f, rows[k], tiles);
+        account(t, f, s, rows[k], tiles);
     }
 }
 
@@ -523,9 +553,9 @@ int enqueue_batch(const jr_frame* frames, int32_t n, int32_t* out_base, int64_t 
     int dev;
     DeviceInfo info;
     if ((rc = current_device(&dev, &info))) return rc;
+    route_rational(frames, n, s);
     Table t;
     build_table(frames, n, s, t);
-    route_rational(t, s);
     const int blocks = grid_blocks(info, s, t.total_tiles);
     const bool queues = s.persistent && s.kernel != JR_KERNEL_PLAIN;
     if (n == 1 && !queues) {
@@ -616,9 +646,9 @@ int enqueue_batch_noalloc(const jr_frame* frames, int32_t n, int32_t* out_base, 
     unsigned long long* ctr = static_cast<unsigned long long*>(base);
     DevFrame* table = reinterpret_cast<DevFrame*>(static_cast<char*>(base) + jr::kCounterBytes);
     std::lock_guard<std::mutex> g(g_na_mu);
+    route_rational(frames, n, s);
     TableStats t;
     build_rows(frames, n, s, g_na_rows, g_na_idx, t);
-    route_rational(t, s);
     const int blocks = grid_blocks(info, s, t.total_tiles);
     jr::PersistentArgs args = make_args(t, n == 1 ? nullptr : table, out_base, ctr, n, blocks, s);
     if (n == 1) {
@@ -757,8 +787,8 @@ jr::CardioidArgs cardioid_args(const jr_cardioid_path& p, const jr_schedule& s, 
     g.frames = p.frames;
     t = TableStats();
     t.total_tiles = tiles * p.frames;
-    t.total_cost = frame_cost(f) * (double)p.frames;
-    t.max_tile_cost = frame_cost(f) / (double)tiles;
+    t.total_cost = launch_cost(f, s) * (double)p.frames;
+    t.max_tile_cost = launch_cost(f, s) / (double)tiles;
     t.dtmask = 1 << p.dtype;
     return g;
 }
@@ -995,9 +1025,9 @@ int jr_plan_create(const jr_frame* frames, int32_t n, int32_t* out_base, int64_t
     int dev;
     DeviceInfo info;
     if ((rc = current_device(&dev, &info))) return rc;
+    route_rational(frames, n, s);
     Table t;
     build_table(frames, n, s, t);
-    route_rational(t, s);
     jr_plan* p = new jr_plan();
     p->dev = dev;
     p->nframes = n;
