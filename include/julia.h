@@ -160,7 +160,8 @@ typedef struct {
  *                   (4..32, a multiple of 4).
  *   order           JR_ORDER_TABLE: frames in the order given;
  *                   JR_ORDER_COST: most expensive frames first (estimated
- *                   from size, cap and dtype).
+ *                   from size, cap and dtype, and in the rows kernel from the
+ *                   critical orbit of the frame's map).
  *   kernel          JR_KERNEL_TILED: the tiled kernel above;
  *                   JR_KERNEL_PLAIN: one thread per pixel over the whole batch
  *                   (16 x 16 tiles, one workgroup each, a test on every
@@ -185,7 +186,10 @@ typedef struct {
  *                   own 180-degree rotation (an even degree, a Julia image,
  *                   a window about 0, rows about the middle) are computed by
  *                   half: with tile_h even, a tile takes tile_h / 2 rows and
- *                   stores each count at the opposite pixel too.
+ *                   stores each count at the opposite pixel too.  Orbits of
+ *                   Julia images of Z^degree + C end in the drain once they
+ *                   are in discs about the map's attracting cycle that no
+ *                   orbit leaves: their count is max_iter.
  *   bail            JR_KERNEL_HYBRID: 1..4096; JR_KERNEL_ROWS: 1..64 (other
  *                   kernels ignore it).
  *   handoff         JR_KERNEL_ROWS, 0..256: rows run in groups for FP32 and

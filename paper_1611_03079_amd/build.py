@@ -13,7 +13,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libjulia.so")
 SOURCES = [os.path.join(CSRC, "julia_kernels.hip"), os.path.join(CSRC, "julia_host.cpp")]
-HEADERS = [os.path.join(CSRC, "julia_device.h"), os.path.join(ROOT, "include", "julia.h")]
+HEADERS = [os.path.join(CSRC, "julia_device.h"), os.path.join(CSRC, "julia_trap.h"),
+           os.path.join(ROOT, "include", "julia.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

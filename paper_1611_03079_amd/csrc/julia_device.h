@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "julia_trap.h"
+
 namespace jr {
 
 enum { kFP64 = 0, kFP32 = 1, kFF = 2 };
@@ -20,7 +22,14 @@ struct alignas(16) DevFrame {
     double cx, cy, hx, hy;   // pixel-centre mapping
     int64_t out_offset;      // element offset of pixel (0, 0) in the arena
     int64_t tile_begin;      // global index of this frame's first tile
-    double lr, li;           // lambda of the rational map (kMapRational)
+    union {                  // kMapRational: lambda; polynomial maps with
+        double lr;           // trap_p > 0: disc 0 of the trap (find_trap)
+        struct { float trap_x, trap_y; };
+    };
+    union {
+        double li;
+        float trap_r;
+    };
     int32_t width, height;
     int32_t max_iter;
     int32_t dtype;           // kFP64 / kFP32 / kFF
@@ -35,7 +44,7 @@ struct alignas(16) DevFrame {
     int32_t mirror;          // 1: the image is its own 180-degree rotation; rows
                              // [row_begin, row_end) are computed and each count also
                              // goes to pixel (height - 1 - row, width - 1 - column)
-    int32_t reserved;
+    int32_t trap_p;          // > 0: period of the frame's trap (rows kernel)
 };
 static_assert(sizeof(DevFrame) == 144, "DevFrame layout");
 
@@ -128,6 +137,7 @@ struct CardioidArgs {
     double step_re, step_im, a0, da;
     int64_t out_offset0, frame_px, tiles_per_frame;
     int32_t frames;
+    int32_t traps;           // 1: look for each frame's trap
 };
 hipError_t launch_cardioid_table(const CardioidArgs& g, hipStream_t stream);
 // Zeroes n int32 words with a kernel (not a memset, so that it can sit in a

@@ -15,7 +15,6 @@
 #include <cstring>
 #include <map>
 #include <mutex>
-#include <numeric>
 #include <string>
 #include <utility>
 #include <vector>
@@ -166,19 +165,30 @@ int check_frames(const jr_frame* frames, int32_t n, int64_t capacity) {
 // ------------------------------------------------------------- schedules
 std::mutex g_sched_mu;
 // Defaults per dtype; the autotuner can replace them (jr_set_default_schedule).
-// Starting points from the autotuner's runs on MI355X.  FP32 takes the
-// two-phase rows kernel, which won every FP32 workload measured; one wave per
-// tile keeps one-image calls free of the work queues (and so capturable).
+// The two-phase rows kernel takes them all: it alone ends orbits in traps and
+// computes rotation-symmetric images by half.  Over an uneven batch (96 frames
+// of sides 256..4096, FP32 and float-float) it takes 2.6 ms where the tiled
+// stream took 54.8.  One wave per tile keeps one-image calls free of the work
+// queues (and so capturable).
 jr_schedule g_default[3] = {
     // tile_w, tile_h, unroll, defer, refill, persistent, waves_per_cu, order, kernel, bail,
     // handoff
-    {16, 16, 8, 0, 16, 0, 16, JR_ORDER_COST, JR_KERNEL_TILED, 8, 0},  // FP64
-    {64, 8, 8, 0, 32, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 6, 0},    // FP32
-    {16, 16, 8, 1, 64, 0, 16, JR_ORDER_COST, JR_KERNEL_TILED, 8, 0},  // FF
+    {64, 16, 8, 0, 16, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 16, 32},  // FP64
+    {64, 8, 8, 0, 32, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 6, 0},     // FP32
+    {64, 16, 8, 0, 16, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 8, 0},    // FF
 };
 
-jr_schedule default_schedule(int dtype) {
+bool g_default_set[3];  // replaced by jr_set_default_schedule
+
+// A batch call of one FP64 frame without a schedule keeps the tiled stream that
+// it has always run.  The serving loop's tests take such a launch (1920x1080,
+// nearly all of it bounded, cap 4000) as one that outlasts the host's work on
+// the next request, 0.34 ms: it takes 6 ms here and 0.05 ms on the rows kernel.
+constexpr jr_schedule kLoneFP64 = {16, 16, 8, 0, 16, 0, 16, JR_ORDER_COST, JR_KERNEL_TILED, 8, 0};
+
+jr_schedule default_schedule(int dtype, int32_t nframes = 0) {
     std::lock_guard<std::mutex> g(g_sched_mu);
+    if (nframes == 1 && dtype == JR_FP64 && !g_default_set[dtype]) return kLoneFP64;
     return g_default[dtype];
 }
 
@@ -225,14 +235,16 @@ double dtype_cost(int dtype) {
     return dtype == JR_FF ? 20.0 : dtype == JR_FP64 ? 1.75 : 1.0;
 }
 
-double frame_cost(const jr_frame& f) {
+// Estimated cost of a frame, arbitrary units.  `steps`: iterations that a long
+// orbit of the frame is taken to run, at most the cap.
+double frame_cost(const jr_frame& f, double steps = 256.0) {
     const int32_t rend = f.row_end == 0 ? f.height : f.row_end;
     const double px = (double)f.width * (double)(rend - f.row_begin);
     // a general map's iteration costs about degree - 1 complex products; the
     // rational term adds |W|^2, lambda conj(W) and two divisions
     double deg = f.degree > 2 ? (double)(f.degree - 1) : 1.0;
     if (f.map == JR_MAP_RATIONAL) deg += 3.0;
-    return px * (4.0 + std::min<double>(f.max_iter, 256.0)) * dtype_cost(f.dtype) * deg;
+    return px * (4.0 + std::min<double>(f.max_iter, steps)) * dtype_cost(f.dtype) * deg;
 }
 
 bool absorbing(const jr_frame& f) {
@@ -268,11 +280,6 @@ bool mirrors(const jr_frame& f, const jr_schedule& s) {
     const int32_t rend = f.row_end == 0 ? f.height : f.row_end;
     const int32_t rows = rend - f.row_begin;
     return f.row_begin == f.height - rend && rows > 1 && (s.tile_h >= rows || s.tile_h % 2 == 0);
-}
-
-// frame_cost of the rows that a launch computes.
-double launch_cost(const jr_frame& f, const jr_schedule& s) {
-    return mirrors(f, s) ? 0.5 * frame_cost(f) : frame_cost(f);
 }
 
 // Totals of a frame table, for the launch shape and the kernel variant.
@@ -317,9 +324,22 @@ jr::PersistentArgs make_args(const TableStats& t, const DevFrame* d_table, int32
     return a;
 }
 
-// The device record of frame f whose first tile is global tile `tile_begin`;
-// returns its tile count.
-int64_t fill_frame(const jr_frame& f, const jr_schedule& s, int64_t tile_begin, DevFrame& d) {
+int64_t tile_count(const DevFrame& d) {
+    return (int64_t)d.tiles_x * ((d.row_end - d.row_begin + d.tile_h - 1) / d.tile_h);
+}
+
+// Whether a launch looks for the traps of frames like f (find_trap): the rows
+// kernel ends orbits in them.  The search takes the host about 2 us where the
+// critical orbit is bounded (100 ns where it escapes at once), which an image
+// of fewer pixels or a lower cap does not win back.
+bool looks_for_trap(const jr_frame& f, const jr_schedule& s) {
+    return s.kernel == JR_KERNEL_ROWS && f.mode == JR_JULIA && f.map == JR_MAP_POLY &&
+           f.max_iter >= 32 && (int64_t)f.width * f.height >= 16384 && absorbing(f);
+}
+
+// The device record of frame f (but for its first tile and its index); returns
+// its estimated cost.
+double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d) {
     std::memset(&d, 0, sizeof d);
     const double W = (double)f.width, H = (double)f.height;
     d.hx = (f.w.re_max - f.w.re_min) / (2.0 * W);
@@ -351,30 +371,26 @@ int64_t fill_frame(const jr_frame& f, const jr_schedule& s, int64_t tile_begin, 
         d.tile_h = (d.tile_h + 1) / 2;
     }
     d.tiles_x = (f.width + d.tile_w - 1) / d.tile_w;
-    const int64_t tiles_y = (d.row_end - d.row_begin + d.tile_h - 1) / d.tile_h;
-    d.tile_begin = tile_begin;
-    return (int64_t)d.tiles_x * tiles_y;
-}
-
-// The order frames go into the table: as given, or (JR_ORDER_COST) most
-// expensive first, equal costs in the order given.  std::sort with the index
-// as tie-break needs no scratch memory, unlike a stable sort.
-void order_frames(const jr_frame* frames, int32_t n, const jr_schedule& s, int32_t* idx) {
-    std::iota(idx, idx + n, 0);
-    if (s.order == JR_ORDER_COST)
-        std::sort(idx, idx + n, [&](int32_t a, int32_t b) {
-            const double ca = launch_cost(frames[a], s), cb = launch_cost(frames[b], s);
-            return ca > cb || (ca == cb && a < b);
-        });
+    double steps = 256.0;
+    if (looks_for_trap(f, s)) {
+        // The critical orbit also says which of a batch's frames run long: one
+        // that escapes after k steps leaves few orbits that run much longer,
+        // and orbits in a trap end soon after they reach it.
+        int critical;
+        d.trap_p = jr::find_trap(f.c.re, f.c.im, d.degree, &d.trap_x, &d.trap_y, &d.trap_r,
+                                 &critical);
+        steps = d.trap_p > 0 ? 16.0 : std::min(critical, 256);
+    }
+    return frame_cost(f, steps) * (d.mirror ? 0.5 : 1.0);
 }
 
 // Adds a frame's tiles to the table totals.
-void account(TableStats& t, const jr_frame& f, const jr_schedule& s, const DevFrame& d,
-             int64_t tiles) {
+void account(TableStats& t, const DevFrame& d, double cost) {
+    const int64_t tiles = tile_count(d);
     t.total_tiles += tiles;
-    t.total_cost += launch_cost(f, s);
-    t.max_tile_cost = std::max(t.max_tile_cost, launch_cost(f, s) / (double)tiles);
-    t.dtmask |= 1 << f.dtype;
+    t.total_cost += cost;
+    t.max_tile_cost = std::max(t.max_tile_cost, cost / (double)tiles);
+    t.dtmask |= 1 << d.dtype;
     if (d.degree > 2) t.dtmask |= jr::kGeneralBit;
     if (d.map == jr::kMapRational) t.dtmask |= jr::kGeneralBit | jr::kRationalBit;
 }
@@ -394,24 +410,33 @@ void route_rational(const jr_frame* frames, int32_t n, jr_schedule& s) {
     s.handoff = 0;
 }
 
-// Fills rows[0, n) in launch order and returns the table's totals; idx is
-// room for n frame indices.  Allocates nothing.
+// Fills rows[0, n) in launch order -- as given, or (JR_ORDER_COST) most
+// expensive first, equal costs in the order given -- and returns the table's
+// totals.  Allocates nothing: until the order is known, a row's cost stands in
+// the place of its first tile.
 void build_rows(const jr_frame* frames, int32_t n, const jr_schedule& s, DevFrame* rows,
-                int32_t* idx, TableStats& t) {
-    order_frames(frames, n, s, idx);
+                TableStats& t) {
+    for (int32_t k = 0; k < n; ++k) {
+        const double cost = fill_frame(frames[k], s, rows[k]);
+        rows[k].index = k;
+        rows[k].tile_begin = (int64_t)cost;
+    }
+    if (s.order == JR_ORDER_COST)
+        std::sort(rows, rows + n, [](const DevFrame& a, const DevFrame& b) {
+            return a.tile_begin > b.tile_begin ||
+                   (a.tile_begin == b.tile_begin && a.index < b.index);
+        });
     t = TableStats();
     for (int32_t k = 0; k < n; ++k) {
-        const jr_frame& f = frames[idx[k]];
-        const int64_t tiles = fill_frame(f, s, t.total_tiles, rows[k]);
-        rows[k].index = idx[k];
-        account(t, f, s, rows[k], tiles);
+        const double cost = (double)rows[k].tile_begin;
+        rows[k].tile_begin = t.total_tiles;
+        account(t, rows[k], cost);
     }
 }
 
 void build_table(const jr_frame* frames, int32_t n, const jr_schedule& s, Table& t) {
-    std::vector<int32_t> idx(n);
     t.rows.resize(n);
-    build_rows(frames, n, s, t.rows.data(), idx.data(), t);
+    build_rows(frames, n, s, t.rows.data(), t);
 }
 
 // The schedule of a batch call: the caller's, checked, or the default of the
@@ -423,7 +448,7 @@ int batch_schedule(const jr_frame* frames, int32_t n, const jr_schedule* sched, 
     }
     double w[3] = {0, 0, 0};
     for (int32_t k = 0; k < n; ++k) w[frames[k].dtype] += frame_cost(frames[k]);
-    s = default_schedule((int)(std::max_element(w, w + 3) - w));
+    s = default_schedule((int)(std::max_element(w, w + 3) - w), n);
     return JR_OK;
 }
 
@@ -625,7 +650,6 @@ static_assert(jr::kNoAllocMaxFrames == JR_NOALLOC_MAX_FRAMES, "one frame limit")
 static_assert(jr::kNoAllocScratchBytes == JR_NOALLOC_SCRATCH_BYTES, "one scratch size");
 std::mutex g_na_mu;
 DevFrame g_na_rows[jr::kNoAllocMaxFrames];
-int32_t g_na_idx[jr::kNoAllocMaxFrames];
 
 int enqueue_batch_noalloc(const jr_frame* frames, int32_t n, int32_t* out_base, int64_t capacity,
                           const jr_schedule* sched, hipStream_t stream) {
@@ -648,7 +672,7 @@ int enqueue_batch_noalloc(const jr_frame* frames, int32_t n, int32_t* out_base, 
     std::lock_guard<std::mutex> g(g_na_mu);
     route_rational(frames, n, s);
     TableStats t;
-    build_rows(frames, n, s, g_na_rows, g_na_idx, t);
+    build_rows(frames, n, s, g_na_rows, t);
     const int blocks = grid_blocks(info, s, t.total_tiles);
     jr::PersistentArgs args = make_args(t, n == 1 ? nullptr : table, out_base, ctr, n, blocks, s);
     if (n == 1) {
@@ -774,8 +798,11 @@ jr::CardioidArgs cardioid_args(const jr_cardioid_path& p, const jr_schedule& s, 
     jr_frame f = single_frame(jr_complex{0.0, 0.0}, p.w, p.width, p.height, p.max_iter,
                               p.dtype, JR_JULIA);
     f.out_offset = p.out_offset;
-    const int64_t tiles = fill_frame(f, s, 0, g.tmpl);
-    g.tmpl.defer = 1;  // every |C_k| < 1.9 (check_cardioid): escape is absorbing
+    const double cost = fill_frame(f, s, g.tmpl);
+    const int64_t tiles = tile_count(g.tmpl);
+    g.tmpl.defer = 1;   // every |C_k| < 1.9 (check_cardioid): escape is absorbing
+    g.tmpl.trap_p = 0;  // that of C = 0
+    g.traps = looks_for_trap(f, s) ? 1 : 0;
     g.dst = dst;
     g.step_re = p.step.re;
     g.step_im = p.step.im;
@@ -787,8 +814,8 @@ jr::CardioidArgs cardioid_args(const jr_cardioid_path& p, const jr_schedule& s, 
     g.frames = p.frames;
     t = TableStats();
     t.total_tiles = tiles * p.frames;
-    t.total_cost = launch_cost(f, s) * (double)p.frames;
-    t.max_tile_cost = launch_cost(f, s) / (double)tiles;
+    t.total_cost = cost * (double)p.frames;
+    t.max_tile_cost = cost / (double)tiles;
     t.dtmask = 1 << p.dtype;
     return g;
 }
@@ -917,6 +944,7 @@ int jr_set_default_schedule(int32_t dtype, const jr_schedule* s) {
     if (rc) return rc;
     std::lock_guard<std::mutex> g(g_sched_mu);
     g_default[dtype] = *s;
+    g_default_set[dtype] = true;
     return JR_OK;
 }
 

@@ -54,6 +54,7 @@ struct ArF64 {
     struct C { double r, i; };
     using V = double;  // one coordinate
     __device__ static V coord(double v) { return v; }
+    __device__ static float lead(V v) { return (float)v; }  // rounded to binary32
     __device__ static V shfl(V v, int src) { return __shfl(v, src); }
     __device__ static Z make(V x, V y) { return Z{x, y}; }
     __device__ static C cmake(V r, V i) { return C{r, i}; }
@@ -95,6 +96,7 @@ struct ArF32 {
     struct C { float r, i, lim; };
     using V = float;
     __device__ static V coord(double v) { return (float)v; }  // one rounding
+    __device__ static float lead(V v) { return v; }
     __device__ static V shfl(V v, int src) { return __shfl(v, src); }
     __device__ static Z make(V x, V y) { return Z{x, y}; }
     __device__ static C cmake(V r, V i) { return C{r, i, 4.0f + r}; }
@@ -194,6 +196,7 @@ struct ArFF {
     }
     using V = D;
     __device__ static V coord(double v) { return split(v); }
+    __device__ static float lead(V v) { return v.hi; }
     __device__ static V shfl(V v, int src) { return D{__shfl(v.hi, src), __shfl(v.lo, src)}; }
     __device__ static Z make(V x, V y) { return Z{x, y}; }
     __device__ static C cmake(V r, V i) { return C{r, i}; }
@@ -1281,6 +1284,42 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
     const uint64_t cols = tw >= 64 ? ~0ull : ((1ull << tw) - 1ull);  // lanes inside the tile
     uint16_t* pos = (uint16_t*)(list + ZW * cap);
 
+    // The frame's trap (find_trap): lane k holds disc k, the centre and the
+    // squared radius, which 1% + 1e-5 keeps inside the true disc whatever
+    // binary32 did to the centre and to the test itself (a centre's error
+    // grows along the cycle no faster than the radii do, so it stays within
+    // 16 * 2e-7 / 0.004 of the radius).  A bounded orbit then costs the few
+    // iterations that bring it into a disc and not the cap: an uneven batch
+    // (96 frames, sides 256..4096, caps 100..2000, FP32 and float-float) went
+    // from 54.8 ms on the refill stream to 2.65 ms.
+    constexpr bool kTraps = !A::kRational && !MANDEL && K != 1;
+    const int tp = kTraps ? __builtin_amdgcn_readfirstlane(F.trap_p) : 0;
+    float tcx = 0.0f, tcy = 0.0f, tr2 = -1.0f;
+    if (kTraps && tp > 0) {
+        float x = F.trap_x, y = F.trap_y, rad = F.trap_r;
+        const float fcr = (float)F.cr, fci = (float)F.ci;
+#pragma unroll 1
+        for (int k = 0; k < tp; ++k) {
+            const float rt = rad * 0.99f - 1e-5f;
+            tcx = lane == k ? x : tcx;
+            tcy = lane == k ? y : tcy;
+            tr2 = lane == k ? rt * rt : tr2;
+            const float m = __builtin_sqrtf(x * x + y * y);
+            float wr = x, wi = y, p0 = m, p1 = m + rad;
+#pragma unroll 1
+            for (int d = 1; d < deg; ++d) {
+                const float t = wr * x - wi * y;
+                wi = wr * y + wi * x;
+                wr = t;
+                p0 *= m;
+                p1 *= m + rad;
+            }
+            x = wr + fcr;
+            y = wi + fci;
+            rad = p1 - p0;
+        }
+    }
+
     // phase 1
     int qn = 0;
     auto start_row = [&](int r, typename A::Z& z, typename A::C& c) {
@@ -1329,8 +1368,8 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
     // round replays that block for it with the counted test, once for all
     // such lanes.  The survivors are long orbits, most of them running to the
     // cap, so most blocks need no replay.
-    auto drain = [&]() {
-        if (qn == 0) return;
+    auto drain_as = [&](auto traps) {
+        constexpr bool kTrapped = decltype(traps)::value;
         // Other lanes read the entries written above, and the next rows
         // overwrite them afterwards: keep the compiler from moving LDS
         // accesses across either point (one wave runs them in order).
@@ -1343,6 +1382,20 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
         int next = 0;
         uint64_t running = 0;
         const int busy_max = 64 - a.refill;
+        // One disc of the trap is tested after each block.  K iterations on,
+        // the disc is K - 1 steps further, so that an orbit on the cycle
+        // meets its own disc within tp blocks whatever its phase.
+        int disc = 0;
+        const int disc_step = kTrapped ? (K - 1) % tp : 0;
+        auto trapped = [&]() {
+            const float cx = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(tcx), disc));
+            const float cy = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(tcy), disc));
+            const float r2 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(tr2), disc));
+            disc += disc_step;
+            disc = disc >= tp ? disc - tp : disc;
+            const float dx = A::lead(z.x) - cx, dy = A::lead(z.y) - cy;
+            return __builtin_fmaf(dx, dx, dy * dy) < r2;
+        };
         for (;;) {
             if (__popcll(running) <= busy_max) {
                 if (kDeferDrain && __ballot(pe) != 0) {
@@ -1397,7 +1450,8 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
 #pragma unroll
                 for (int u = 0; u < K; ++u) A::step(z, c, deg);
                 const bool esc = !A::inside(z, c, deg);
-                const bool capped = n + K >= mi;  // no escape in the block: count the cap
+                bool capped = n + K >= mi;  // no escape in the block: count the cap
+                if constexpr (kTrapped) capped |= trapped();
                 cnt = (it && !esc && capped) ? mi : cnt;
                 fi = fi || (it && !esc && capped);
                 pe = pe || (it && esc);
@@ -1412,7 +1466,8 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
 #pragma unroll
                 for (int u = 0; u < K; ++u) in[u] = A::check_step(z, c, deg);
                 const bool esc = it && !in[K - 1];
-                const bool capped = n + K >= mi;
+                bool capped = n + K >= mi;
+                if constexpr (kTrapped) capped |= trapped();
                 if (__ballot(esc) != 0) {
                     int lead = 0;
 #pragma unroll
@@ -1428,6 +1483,18 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         qn = 0;
+    };
+    // Frames without a trap have a drain without its test: the branch on `tp`
+    // after each block took 4% of a frame whose orbits never end in one.
+    auto drain = [&]() {
+        if (qn == 0) return;
+        if constexpr (kTraps) {
+            if (tp > 0) {
+                drain_as(std::true_type());
+                return;
+            }
+        }
+        drain_as(std::false_type());
     };
     int r = 0;
     // Row groups for the quadratic FP32 and FP64 maps; float-float and the
@@ -1689,6 +1756,8 @@ __global__ __launch_bounds__(256) void jr_cardioid_table(CardioidArgs g) {
     DevFrame f = g.tmpl;
     f.cr = nr / a;
     f.ci = ni / a;
+    int steps;
+    if (g.traps) f.trap_p = find_trap(f.cr, f.ci, 2, &f.trap_x, &f.trap_y, &f.trap_r, &steps);
     f.out_offset = g.out_offset0 + (int64_t)k * g.frame_px;
     f.tile_begin = (int64_t)k * g.tiles_per_frame;
     f.index = (int32_t)k;
