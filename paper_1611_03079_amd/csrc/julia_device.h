@@ -63,6 +63,7 @@ struct PersistentArgs {
     unsigned long long* ctr;
     int64_t total_tiles;
     int64_t granules;
+    double frames_per_tile;  // nframes / total_tiles: where equal frames' tiles lie
     int32_t nframes;
     int32_t granule;     // tiles per granule
     int32_t refill;

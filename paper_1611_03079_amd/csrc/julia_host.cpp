@@ -313,6 +313,7 @@ jr::PersistentArgs make_args(const TableStats& t, const DevFrame* d_table, int32
     a.ctr = ctr;
     a.total_tiles = t.total_tiles;
     a.nframes = n;
+    a.frames_per_tile = (double)n / (double)t.total_tiles;
     a.granule = granule_size(t, blocks);
     a.granules = (t.total_tiles + a.granule - 1) / a.granule;
     a.refill = s.refill;
@@ -365,6 +366,10 @@ double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d) {
     const int32_t th = s.kernel == JR_KERNEL_PLAIN ? 16 : s.tile_h;
     d.tile_w = std::min(tw, f.width);
     d.tile_h = std::min(th, d.row_end - d.row_begin);
+    // a tile of the rows kernel spans less than 2^30 pixels of the image, so that
+    // its byte offsets fit 32 bits (widths from 2^24 on have lower tiles)
+    if (s.kernel == JR_KERNEL_ROWS)
+        d.tile_h = std::min(d.tile_h, std::max(1, ((1 << 30) - 64) / f.width));
     if (mirrors(f, s)) {
         d.mirror = 1;
         d.row_end = d.row_begin + (d.row_end - d.row_begin + 1) / 2;

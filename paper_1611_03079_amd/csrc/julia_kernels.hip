@@ -1237,18 +1237,39 @@ __device__ __forceinline__ typename A::Z list_get(const uint32_t* list, int cap,
 // single by-value PersistentArgs argument sits at offset 0).  A function that
 // is not inlined and takes the by-value argument by reference gets a copy of
 // it in per-lane stack memory; through this reference it reads the arguments
-// with scalar loads instead.  The general and rational maps' tiles, which
-// are not inlined, take this; the quadratic maps' tiles are inlined and take
-// the by-value argument, which keeps the hot loop's registers as they were
-// (the kernel-argument reference there cost 16 more vector registers and
-// about 10% of the parameter path's time).
+// with scalar loads instead.
 typedef const __attribute__((address_space(4))) PersistentArgs CArgs;
 __device__ __forceinline__ CArgs& kernel_args() {
     return *(CArgs*)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
+// The frame of tile t.  Frames of equal size put it at the proportional place,
+// which two scalar loads confirm; otherwise the lanes look at 64 frames at a
+// time, one vector load for up to 64 frames and two for up to 4096, where a
+// binary search is a chain of scalar loads with a dozen scalar instructions each.
+__device__ __forceinline__ int frame_of_tile(CFrame* frames, int nframes, int64_t t,
+                                             double frames_per_tile) {
+    if (nframes == 1) return 0;
+    const int guess =
+        __builtin_amdgcn_readfirstlane(min((int)(((double)t + 0.5) * frames_per_tile), nframes - 1));
+    const int64_t b0 = frames[guess].tile_begin;
+    const int64_t b1 = frames[min(guess + 1, nframes - 1)].tile_begin;
+    if (b0 <= t && (t < b1 || guess == nframes - 1)) return guess;
+    int lo = 0, n = nframes;
+    while (n > 1) {
+        const int step = (n + 63) >> 6;
+        const int at = lane_id() * step;
+        bool below = false;
+        if (at < n) below = frames[lo + at].tile_begin <= t;
+        const int k = __popcll(__ballot(below)) - 1;  // frame lo starts at or before t
+        lo += k * step;
+        n = min(step, n - k * step);
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
 template <class A, int K, int MANDEL, int COLOR, int LROWS, int DD, class Args>
-__device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* list,
+__device__ __forceinline__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* list,
                           int32_t* done_at) {
     constexpr int cap = 64 * LROWS;  // list entries
     // deferred drain blocks need escape to be absorbing (K > 1 means it is)
@@ -1270,18 +1291,23 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
     const V xl = A::coord(pixel_re(F.cx, F.hx, col0 + min(lane, tw - 1), W));
     const V yl = A::coord(pixel_im(F.cy, F.hy, row0 + min(lane, th - 1), F.height));
     const typename A::C cj = frame_c<A>(F);
-    int32_t* tout = a.out_base + F.out_offset + ((int64_t)row0 * W + col0);
-    // The image's 180-degree rotation takes pixel (r, lane) of the tile to
-    // mout[-(r * W + lane)].  A middle row that is its own mirror (odd
-    // heights) is stored twice with the same values.  Half the orbits, the
-    // same bytes: 256 FP32 frames of 1920x1080 went from 903 to 600 us (444
-    // with the mirrored stores left out, so they are now what a light frame
-    // waits for), 64 FP64 frames from 562 to 300 us.
+    // Pixel (r, c) of the tile is tout[r * W + c], and the image's 180-degree
+    // rotation takes it to mout[mlast - (r * W + c)].  Both indices times four
+    // fit 32 bits (the host keeps tiles of very wide frames low enough), so that
+    // a store takes its base from scalar registers.  A middle row that is its
+    // own mirror (odd heights) is stored twice with the same values.  Half the
+    // orbits, the same bytes: 256 FP32 frames of 1920x1080 went from 903 to 600
+    // us (444 with the mirrored stores left out, so they are now what a light
+    // frame waits for), 64 FP64 frames from 562 to 300 us.
+    int32_t* const out = a.out_base + F.out_offset;
+    int32_t* const tout = out + (row0 * W + col0);
     const bool mirror = __builtin_amdgcn_readfirstlane(F.mirror) != 0;
-    int32_t* mout = a.out_base + F.out_offset +
-                    ((int64_t)(F.height - 1 - row0) * W + (W - 1 - col0));
-    const bool col_ok = lane < tw;
+    const int mlast = (th - 1) * W + tw - 1;
+    int32_t* const mout = out + ((F.height - row0 - th) * W + (W - col0 - tw));
     const uint64_t cols = tw >= 64 ? ~0ull : ((1ull << tw) - 1ull);  // lanes inside the tile
+    // Lanes past the tile's width repeat its last column in all they do, so the
+    // row ends need no mask: such a lane stores the same value at the same place.
+    const int col = min(lane, tw - 1);
     uint16_t* pos = (uint16_t*)(list + ZW * cap);
 
     // The frame's trap (find_trap): lane k holds disc k, the centre and the
@@ -1332,30 +1358,51 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
             c = cj;
         }
     };
-    // A pixel survives when it is inside for all `done` iterates its group
-    // ran (lead = done) and the cap lies beyond them; one compare against the
-    // lane's bound gives the survivors' mask directly.  Finished pixels store,
+    // A pixel survives when it is inside for all `done` iterates its rows ran
+    // (lead = done) and the cap lies beyond them; one compare against a uniform
+    // bound gives the survivors' mask directly.  Finished pixels store,
     // survivors append.  An entry's position word holds the row and column
     // in the tile and, in its top four bits, done / 4 - 1 (done is a multiple
     // of 4 from 4 to 64 where K > 1; where K = 1 it is P = 1 and the bits are
-    // unused).
-    auto finish_row = [&](int r, int lead, const typename A::Z& z, int done) {
-        const int p_lane = (col_ok && done < mi) ? done : 0x7fffffff;
-        const bool sv = lead >= p_lane;
-        const bool fin = col_ok && !sv;
-        const uint64_t m = __ballot(sv);
-        if (fin) {
-            const int32_t v = shade<COLOR>(a, min(lead, mi));
-            store_at(tout + (int64_t)r * W, lane, v);
-            if (mirror) store_at(mout - (int64_t)r * W - 63, 63 - lane, v);
+    // unused).  Rows without survivors, the most of a light image, store
+    // unmasked: the scalar unit, one instruction per cycle for the four SIMDs
+    // of a CU, is what bounds light tiles (at tiles of 64x4 pixels of count 0 a
+    // wave issued 417 scalar and 230 vector instructions, 0.92 scalar ones per
+    // cycle), so the row ends count in scalar instructions.
+    auto put = [&](int at, int32_t v) {
+        store_at(tout, at, v);
+        if (mirror) store_at(mout, mlast - at, v);
+    };
+    auto finish_rows = [&](auto rows, int r, const int* lead, const typename A::Z* z, int done) {
+        constexpr int R = decltype(rows)::value;
+        const int bound = done < mi ? done : 0x7fffffff;
+        uint64_t sv[R], any = 0;
+        int32_t v[R];
+#pragma unroll
+        for (int g = 0; g < R; ++g) {
+            sv[g] = __ballot(lead[g] >= bound);
+            any |= sv[g];
+            v[g] = shade<COLOR>(a, min(lead[g], mi));
         }
-        if (sv) {
-            const int e = qn + lanes_below(m);
-            list_put<A>(list, cap, e, z);
-            const int k = K == 1 ? 0 : (done >> 2) - 1;
-            pos[e] = (uint16_t)((k << 12) | (r << 6) | lane);
+        const int at = r * W + col;
+        if (any == 0) {
+#pragma unroll
+            for (int g = 0; g < R; ++g) put(at + g * W, v[g]);
+            return;
         }
-        qn += __popcll(m);
+#pragma unroll
+        for (int g = 0; g < R; ++g) {
+            const bool stays = lead[g] >= bound;
+            const uint64_t m = sv[g] & cols;
+            if (!stays) put(at + g * W, v[g]);
+            if (stays && lane < tw) {
+                const int e = qn + lanes_below(m);
+                list_put<A>(list, cap, e, z[g]);
+                const int k = K == 1 ? 0 : (done >> 2) - 1;
+                pos[e] = (uint16_t)((k << 12) | ((r + g) << 6) | lane);
+            }
+            qn += __popcll(m);
+        }
     };
     // Phase 2: the refill stream over the list's entries, in blocks of K;
     // idle lanes read the next entries straight from the list, and C is the
@@ -1411,12 +1458,7 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
                     }
                 }
                 if (fi) {
-                    // r * W + col fits an int (a frame holds < 2^31 pixels),
-                    // but four times it may not fit 32 bits: index, so that
-                    // the address is formed in 64 bits.
-                    const int32_t v = shade<COLOR>(a, cnt);
-                    tout[off] = v;
-                    if (mirror) mout[-(int64_t)off] = v;
+                    put(off, shade<COLOR>(a, cnt));
                     fi = false;
                 }
                 if (next < qn) {
@@ -1425,18 +1467,18 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
                     const int ee = min(e, qn - 1);
                     const typename A::Z zl = list_get<A>(list, cap, ee);
                     const uint32_t id = pos[ee];
-                    const int r = (int)((id >> 6) & 63u);
-                    const int col = (int)(id & 63u);
+                    const int row = (int)((id >> 6) & 63u);
+                    const int pc = (int)(id & 63u);
                     const int done = K == 1 ? P : (int)((id >> 12) + 1u) * 4;
                     V cx = zero, cy = zero;
                     if (MANDEL) {
-                        cx = A::shfl(xl, col);
-                        cy = A::shfl(yl, r);
+                        cx = A::shfl(xl, pc);
+                        cy = A::shfl(yl, row);
                     }
                     if (!it && e < qn) {
                         z = zl;
                         if (MANDEL) c = A::cmake(cx, cy);
-                        off = r * W + col;
+                        off = row * W + pc;
                         n = done;
                         it = true;
                     }
@@ -1512,8 +1554,7 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
         // pixels inside the tile are still inside the disc: with 0, once all
         // have escaped (absorbing: later iterates would count nothing);
         // otherwise the few still running go to the list with the count so
-        // far instead of holding the wave.  Lanes past the tile's width
-        // repeat its last column and are not counted.
+        // far instead of holding the wave.
         const int handoff = __builtin_amdgcn_readfirstlane(a.handoff);
         for (; r + G <= th; r += G) {
             if (qn + 64 * G > cap) drain();  // room for the group's survivors
@@ -1538,7 +1579,7 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
                 for (int g = 0; g < G; ++g) {
                     const bool in = A::check_step(z[g], c[g], deg);
                     l[g] += in ? 1 : 0;
-                    still += __popcll(__ballot(in) & cols);
+                    still += __popcll(__ballot(in));
                 }
                 return still;
             };
@@ -1563,14 +1604,14 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
                             l[g] += in ? 1 : 0;
                             alive |= __ballot(in);
                         }
-                        if ((alive & cols) == 0) return -k;  // all escaped after k tests
+                        if (alive == 0) return -k;  // all escaped after k tests
                     }
                     int still = 0;
 #pragma unroll
                     for (int g = 0; g < G; ++g) {
                         const bool in = A::check_step(z[g], c[g], deg);
                         l[g] += in ? 1 : 0;
-                        still += __popcll(__ballot(in) & cols);
+                        still += __popcll(__ballot(in));
                     }
                     return still;
                 } else {
@@ -1588,8 +1629,7 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
                     if (trip() <= handoff) break;
                 }
             }
-#pragma unroll
-            for (int g = 0; g < G; ++g) finish_row(r + g, l[g], z[g], done);
+            finish_rows(std::integral_constant<int, G>(), r, l, z, done);
         }
     }
     for (; r < th; ++r) {  // single rows: an odd tile height's last, P = 1, wide types
@@ -1612,13 +1652,19 @@ __device__ void rows_tile(const Args& a, CFrame& F, int64_t t, int P, uint32_t* 
                 if (__ballot(in) == 0) break;
             }
         }
-        finish_row(r, lead, z, done);
+        finish_rows(std::integral_constant<int, 1>(), r, &lead, &z, done);
     }
     drain();
     if (done_at) {  // the frame's progress counter: a middle row is its own mirror
         const int middle = 2 * (row0 + th) - 1 == F.height ? tw : 0;
         add_done(done_at, mirror ? 2 * tw * th - middle : tw * th);
     }
+}
+
+template <class A, int K, int MANDEL, int COLOR, int LROWS, int DD>
+__device__ __attribute__((noinline)) void rows_tile_call(CArgs& a, CFrame& F, int64_t t, int P,
+                                                         uint32_t* list, int32_t* done_at) {
+    rows_tile<A, K, MANDEL, COLOR, LROWS, DD>(a, F, t, P, list, done_at);
 }
 
 // Waves of 64 lanes, one tile at a time (from the dispatcher or the work
@@ -1638,18 +1684,13 @@ __global__ __launch_bounds__(64 * WPB) void jr_rows(PersistentArgs a) {
         WPB == 1 ? lmem
                  : lmem + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * S::wave_words;
     stage_palette<COLOR>(a);
-    Claimer cl;
-    claimer_init(cl, a);
     CFrame* frames = cframes(a);
     CArgs& ka = kernel_args();
-    int f = 0;
     constexpr bool kProgress = (DTMASK & kProgressBit) != 0;
-    for (;;) {
-        if (kProgress && stop_requested(a.stop)) break;
-        const int64_t t = next_tile(cl, a);
-        if (t < 0) break;
-        f = find_frame(frames, a.nframes, t, f);
-        CFrame& F = frames[f];
+    constexpr int kTypes = DTMASK & 7;
+    constexpr bool kCalls = (DTMASK & kGeneralBit) != 0 && (kTypes & (kTypes - 1)) != 0;
+    auto tile = [&](int64_t t) {
+        CFrame& F = frames[frame_of_tile(frames, a.nframes, t, a.frames_per_tile)];
         const bool abs = F.defer != 0;
         // The first block's length: the schedule's, rounded up to a multiple
         // of 4 (four iterations per trip), or 1 where escape may not be
@@ -1659,49 +1700,78 @@ __global__ __launch_bounds__(64 * WPB) void jr_rows(PersistentArgs a) {
         const int P = __builtin_amdgcn_readfirstlane(abs ? (a.bail + 3) & ~3 : 1);
         const bool mandel = F.mode == kModeMandelbrot;
         int32_t* const done_at = kProgress && a.done ? a.done + F.index : nullptr;
-#define JR_ROWS(A_, ARGS_)                                                               \
-    do {                                                                                 \
-        if (abs && !mandel) rows_tile<A_, K, 0, COLOR, S::rows, DD>(ARGS_, F, t, P, list, done_at); \
-        else if (abs) rows_tile<A_, K, 1, COLOR, S::rows, DD>(ARGS_, F, t, P, list, done_at);       \
-        else if (!mandel) rows_tile<A_, 1, 0, COLOR, S::rows, 0>(ARGS_, F, t, P, list, done_at);    \
-        else rows_tile<A_, 1, 1, COLOR, S::rows, 0>(ARGS_, F, t, P, list, done_at);                 \
+        // Kernels that hold every dtype and the general maps call their tiles;
+        // in all others the tiles are inlined, and a launch of one dtype has such
+        // a kernel for the general and rational maps too (calls cost registers:
+        // 133 against 60, and 3 waves per SIMD against 8).
+#define JR_ROWS_(A_, K_, M_, D_)                                                            \
+    do {                                                                                    \
+        if constexpr (kCalls)                                                               \
+            rows_tile_call<A_, K_, M_, COLOR, S::rows, D_>(ka, F, t, P, list, done_at);     \
+        else                                                                                \
+            rows_tile<A_, K_, M_, COLOR, S::rows, D_>(a, F, t, P, list, done_at);           \
     } while (0)
-        // quadratic maps: kernels that also hold the general maps call tiles
-        // that are not inlined, which take the arguments in place
-#define JR_ROWS_Q(A_)                          \
-    do {                                       \
-        if constexpr ((DTMASK & kGeneralBit) != 0) \
-            JR_ROWS(A_, ka);                   \
-        else                                   \
-            JR_ROWS(A_, a);                    \
+#define JR_ROWS(A_)                                \
+    do {                                           \
+        if (abs && !mandel) JR_ROWS_(A_, K, 0, DD); \
+        else if (abs) JR_ROWS_(A_, K, 1, DD);       \
+        else if (!mandel) JR_ROWS_(A_, 1, 0, 0);    \
+        else JR_ROWS_(A_, 1, 1, 0);                 \
     } while (0)
         // rational maps: Julia images in FP64 or FP32 (the host checks)
-#define JR_ROWS_R(A_)                                                              \
-    do {                                                                           \
-        if (abs) rows_tile<A_, K, 0, COLOR, S::rows, DD>(ka, F, t, P, list, done_at);      \
-        else rows_tile<A_, 1, 0, COLOR, S::rows, 0>(ka, F, t, P, list, done_at);           \
+#define JR_ROWS_R(A_)                  \
+    do {                               \
+        if (abs) JR_ROWS_(A_, K, 0, DD); \
+        else JR_ROWS_(A_, 1, 0, 0);      \
     } while (0)
-        if ((DTMASK & kRationalBit) && F.map == kMapRational) {
-            if (F.dtype == kFP32)
-                JR_ROWS_R(ArF32R);
-            else
-                JR_ROWS_R(ArF64R);
-        } else if ((DTMASK & kGeneralBit) && F.degree > 2) {
-            if (F.dtype == kFP32)
-                JR_ROWS(ArF32G, ka);
-            else if (F.dtype == kFP64)
-                JR_ROWS(ArF64G, ka);
-            else
-                JR_ROWS(ArFFG, ka);
-        } else if ((DTMASK & (1 << kFP32)) && F.dtype == kFP32)
-            JR_ROWS_Q(ArF32);
-        else if ((DTMASK & (1 << kFP64)) && F.dtype == kFP64)
-            JR_ROWS_Q(ArF64);
-        else if ((DTMASK & (1 << kFF)) && F.dtype == kFF)
-            JR_ROWS_Q(ArFF);
+        constexpr bool k32 = (DTMASK & (1 << kFP32)) != 0, k64 = (DTMASK & (1 << kFP64)) != 0,
+                       kff = (DTMASK & (1 << kFF)) != 0;
+        constexpr bool kG = (DTMASK & kGeneralBit) != 0, kR = (DTMASK & kRationalBit) != 0;
+        if (kR && F.map == kMapRational) {
+            if constexpr (kR && k32) {
+                if (F.dtype == kFP32) JR_ROWS_R(ArF32R);
+            }
+            if constexpr (kR && k64) {
+                if (F.dtype == kFP64) JR_ROWS_R(ArF64R);
+            }
+        } else if (kG && F.degree > 2) {
+            if constexpr (kG && k32) {
+                if (F.dtype == kFP32) JR_ROWS(ArF32G);
+            }
+            if constexpr (kG && k64) {
+                if (F.dtype == kFP64) JR_ROWS(ArF64G);
+            }
+            if constexpr (kG && kff) {
+                if (F.dtype == kFF) JR_ROWS(ArFFG);
+            }
+        } else {
+            if constexpr (k32) {
+                if (F.dtype == kFP32) JR_ROWS(ArF32);
+            }
+            if constexpr (k64) {
+                if (F.dtype == kFP64) JR_ROWS(ArF64);
+            }
+            if constexpr (kff) {
+                if (F.dtype == kFF) JR_ROWS(ArFF);
+            }
+        }
 #undef JR_ROWS
 #undef JR_ROWS_R
-#undef JR_ROWS_Q
+#undef JR_ROWS_
+    };
+    if constexpr (WPB == 1) {
+        // one wave, one dispatched tile: none of the work queues' code
+        if (kProgress && stop_requested(a.stop)) return;
+        tile((int64_t)blockIdx.x);
+    } else {
+        Claimer cl;
+        claimer_init(cl, a);
+        for (;;) {
+            if (kProgress && stop_requested(a.stop)) break;
+            const int64_t t = next_tile(cl, a);
+            if (t < 0) break;
+            tile(t);
+        }
     }
 }
 
@@ -1859,12 +1929,23 @@ static TiledFn pick_rows_mask(int dtmask, bool one_wave, int defer) {
         return one_wave ? jr_rows<K, kGRP, 1, 0> : jr_rows<K, kGRP, 4, 0>;
     }
     if (dtmask & kRationalBit) {
+        constexpr int kGROnly = kGeneralBit | kRationalBit;
         if (dtmask & kColorBit) return jr_rows<K, kGR | kColorBit, 4, 0>;
+        if (one_wave && dtmask == (kGROnly | (1 << kFP64)))
+            return jr_rows<K, kGROnly | (1 << kFP64), 1, 0>;
+        if (one_wave && dtmask == (kGROnly | (1 << kFP32)))
+            return jr_rows<K, kGROnly | (1 << kFP32), 1, 0>;
         return one_wave ? jr_rows<K, kGR, 1, 0> : jr_rows<K, kGR, 4, 0>;
     }
     if (one_wave && dtmask == ((1 << kFP32) | kColorBit))
         return jr_rows<K, (1 << kFP32) | kColorBit, 1, 0>;
     if (one_wave && !(dtmask & kColorBit)) {
+        switch (dtmask) {
+            case (1 << kFP64) | kGeneralBit: return jr_rows<K, (1 << kFP64) | kGeneralBit, 1, 0>;
+            case (1 << kFP32) | kGeneralBit: return jr_rows<K, (1 << kFP32) | kGeneralBit, 1, 0>;
+            case (1 << kFF) | kGeneralBit: return jr_rows<K, (1 << kFF) | kGeneralBit, 1, 0>;
+            default: break;
+        }
         if (dtmask & kGeneralBit) return jr_rows<K, 7 | kGeneralBit, 1, 0>;
         switch (dtmask) {
             case 1 << kFP32: return jr_rows<K, 1 << kFP32, 1, 0>;
