@@ -44,7 +44,8 @@ struct alignas(16) DevFrame {
     int32_t mirror;          // 1: the image is its own 180-degree rotation; rows
                              // [row_begin, row_end) are computed and each count also
                              // goes to pixel (height - 1 - row, width - 1 - column)
-    int32_t trap_p;          // > 0: period of the frame's trap (rows kernel)
+    int32_t trap_p;          // rows kernel, > 0: period of the frame's trap; -1: it has
+                             // none, orbits are looked at for repeated iterates
 };
 static_assert(sizeof(DevFrame) == 144, "DevFrame layout");
 

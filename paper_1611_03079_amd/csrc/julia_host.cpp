@@ -338,6 +338,14 @@ bool looks_for_trap(const jr_frame& f, const jr_schedule& s) {
            f.max_iter >= 32 && (int64_t)f.width * f.height >= 16384 && absorbing(f);
 }
 
+// Whether orbits of a frame without a trap are looked at for repeated iterates.
+// They come once an orbit has converged to its cycle as far as the arithmetic
+// can tell, 24 or 53 bits: about 24 or 53 iterations at a multiplier of 1/2 an
+// iteration, so lower caps do not win the look's cost back (under 2% of a drain).
+bool looks_for_repeats(const jr_frame& f, const jr_schedule& s) {
+    return s.kernel == JR_KERNEL_ROWS && f.max_iter > (f.dtype == JR_FP32 ? 128 : 256);
+}
+
 // The device record of frame f (but for its first tile and its index); returns
 // its estimated cost.
 double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d) {
@@ -385,6 +393,10 @@ double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d) {
         d.trap_p = jr::find_trap(f.c.re, f.c.im, d.degree, &d.trap_x, &d.trap_y, &d.trap_r,
                                  &critical);
         steps = d.trap_p > 0 ? 16.0 : std::min(critical, 256);
+        if (d.trap_p == 0 && critical == jr::kCriticalSteps && looks_for_repeats(f, s))
+            d.trap_p = -1;
+    } else if (looks_for_repeats(f, s)) {
+        d.trap_p = -1;
     }
     return frame_cost(f, steps) * (d.mirror ? 0.5 : 1.0);
 }
@@ -805,8 +817,8 @@ jr::CardioidArgs cardioid_args(const jr_cardioid_path& p, const jr_schedule& s, 
     f.out_offset = p.out_offset;
     const double cost = fill_frame(f, s, g.tmpl);
     const int64_t tiles = tile_count(g.tmpl);
-    g.tmpl.defer = 1;   // every |C_k| < 1.9 (check_cardioid): escape is absorbing
-    g.tmpl.trap_p = 0;  // that of C = 0
+    g.tmpl.defer = 1;  // every |C_k| < 1.9 (check_cardioid): escape is absorbing
+    g.tmpl.trap_p = looks_for_repeats(f, s) ? -1 : 0;  // where a bounded orbit has no trap
     g.traps = looks_for_trap(f, s) ? 1 : 0;
     g.dst = dst;
     g.step_re = p.step.re;

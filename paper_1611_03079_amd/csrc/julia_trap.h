@@ -24,10 +24,11 @@ namespace jr {
 // |W| < 4, one sum, C rounded to binary32); binary64 and float-float by less.
 constexpr int kTrapPeriodMax = 16;
 constexpr double kTrapMinRadius = 0.004;
+constexpr int kCriticalSteps = 512;
 
 // Iterates the critical orbit of Z^degree + C.  Returns the period of a trap
-// (its disc 0 in x, y, r), or 0: none was found within 512 steps.  `steps` is
-// the step at which the critical orbit escaped, 512 if it did not: the higher,
+// (its disc 0 in x, y, r), or 0: none was found within kCriticalSteps.  `steps`
+// is the step at which the critical orbit escaped, kCriticalSteps if it did not: the higher,
 // the longer the image's orbits take.
 JR_HOST_DEVICE inline int find_trap(double cr, double ci, int degree, float* x, float* y,
                                     float* r, int* steps) {
@@ -44,8 +45,8 @@ JR_HOST_DEVICE inline int find_trap(double cr, double ci, int degree, float* x, 
         a = wr + cr;
         b = wi + ci;
     };
-    *steps = 512;
-    for (int stop = 32; stop <= 512; stop *= 4, near *= 0.2) {
+    *steps = kCriticalSteps;
+    for (int stop = 32; stop <= kCriticalSteps; stop *= 4, near *= 0.2) {
         for (; n < stop; ++n) {
             if (!(zx * zx + zy * zy <= 4.0)) {
                 *steps = n;
