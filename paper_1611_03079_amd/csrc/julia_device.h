@@ -28,7 +28,7 @@ struct alignas(16) DevFrame {
     };
     union {
         double li;
-        float trap_r;
+        struct { float trap_r, trap_r1; };  // trap_r1: disc 1's radius where trap_p is 2
     };
     int32_t width, height;
     int32_t max_iter;

@@ -167,7 +167,7 @@ std::mutex g_sched_mu;
 // Defaults per dtype; the autotuner can replace them (jr_set_default_schedule).
 // The two-phase rows kernel takes them all: it alone ends orbits in traps and
 // computes rotation-symmetric images by half.  Over an uneven batch (96 frames
-// of sides 256..4096, FP32 and float-float) it takes 2.6 ms where the tiled
+// of sides 256..4096, FP32 and float-float) it takes 1.8 ms where the tiled
 // stream took 54.8.  One wave per tile keeps one-image calls free of the work
 // queues (and so capturable).
 jr_schedule g_default[3] = {
@@ -391,7 +391,7 @@ double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d) {
         // and orbits in a trap end soon after they reach it.
         int critical;
         d.trap_p = jr::find_trap(f.c.re, f.c.im, d.degree, &d.trap_x, &d.trap_y, &d.trap_r,
-                                 &critical);
+                                 &d.trap_r1, &critical);
         steps = d.trap_p > 0 ? 16.0 : std::min(critical, 256);
         if (d.trap_p == 0 && critical == jr::kCriticalSteps && looks_for_repeats(f, s))
             d.trap_p = -1;

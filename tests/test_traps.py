@@ -27,14 +27,14 @@ def find_trap(tmp_path_factory):
     src = d / "t.cpp"
     src.write_text('#include "julia_trap.h"\n'
                    'extern "C" int find(double a, double b, int d, float* o, int* s) {\n'
-                   '    return jr::find_trap(a, b, d, o, o + 1, o + 2, s); }\n')
+                   '    return jr::find_trap(a, b, d, o, o + 1, o + 2, o + 3, s); }\n')
     lib = str(d / "t.so")
     subprocess.run(["g++", "-O2", "-ffp-contract=off", "-shared", "-fPIC", "-I", CSRC, str(src),
                     "-o", lib], check=True)
     fn = ctypes.CDLL(lib).find
 
     def call(c, degree=2):
-        out, steps = (ctypes.c_float * 3)(), ctypes.c_int()
+        out, steps = (ctypes.c_float * 4)(), ctypes.c_int()
         p = fn(ctypes.c_double(c.real), ctypes.c_double(c.imag), degree, out, ctypes.byref(steps))
         return p, tuple(out), steps.value
     return call
@@ -43,7 +43,7 @@ def find_trap(tmp_path_factory):
 def kernel_discs(p, disc, c, degree):
     """The discs as the kernel forms them, in binary32."""
     f = np.float32
-    x, y, r = (f(v) for v in disc)
+    x, y, r, r1 = (f(v) for v in disc)
     out = []
     for _ in range(p):
         out.append((x, y, r * f(0.99) - f(1e-5)))
@@ -52,7 +52,7 @@ def kernel_discs(p, disc, c, degree):
         for _ in range(1, degree):
             wr, wi = wr * x - wi * y, wr * y + wi * x
             p0, p1 = p0 * m, p1 * (m + r)
-        x, y, r = wr + f(c.real), wi + f(c.imag), p1 - p0
+        x, y, r = wr + f(c.real), wi + f(c.imag), r1 if p == 2 else p1 - p0
     return out
 
 
