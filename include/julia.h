@@ -423,11 +423,12 @@ int jr_set_default_schedule(int32_t dtype, const jr_schedule *sched);
  * those, the smallest pixels_limit >= width*height, or when no entry's
  * pixels_limit covers the image, the one with the largest pixels_limit; with
  * no entry for its dtype and cap it takes the dtype's default.  An entry whose
- * kernel is JR_KERNEL_PLAIN runs the 2-D kernel of julia_render_plain (the
- * colored call runs the batched plain kernel).  An entry with the same
- * (dtype, max_iter_limit, pixels_limit) is replaced; at most 64 entries
- * (JR_EINVAL beyond).  The Python binding installs the autotuner's per-image
- * winners here.
+ * kernel is JR_KERNEL_PLAIN runs with one thread per pixel on a 2-D grid like
+ * julia_render_plain, but with tests in trips of four, half the pixels of an
+ * image that equals its own 180-degree rotation, and orbits ended in traps or
+ * where they repeat an iterate.  An entry with the same (dtype, max_iter_limit,
+ * pixels_limit) is replaced; at most 64 entries (JR_EINVAL beyond).  The Python
+ * binding installs the autotuner's per-image winners here.
  */
 int jr_set_image_schedule(int32_t dtype, int32_t max_iter_limit, int64_t pixels_limit,
                           const jr_schedule *sched);

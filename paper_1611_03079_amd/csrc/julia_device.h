@@ -117,6 +117,18 @@ struct PlainArgs {
     int32_t W, H, max_iter, mode;
 };
 
+// One image on jr_small: the image, and what it may leave out.
+constexpr int kSmallDiscs = 4;
+struct SmallArgs {
+    PlainArgs p;
+    int32_t rows, mirror;  // rows computed; 1: counts go to the opposite pixels too
+    int32_t ends;          // > 0: number of trap discs; -1: orbits end where they repeat;
+                           // -2: the same, and escape may not be absorbing; 0: neither
+    int32_t palette_len;   // > 0: stores palette[min(count, palette_len - 1)]
+    const uint32_t* palette;
+    float x[kSmallDiscs], y[kSmallDiscs], r2[kSmallDiscs];
+};
+
 // Allocation-free batch launches (julia_render_batch_noalloc) keep the queue
 // counters and the frame table in one fixed device array of the library, the
 // counters first (kCounterBytes), then room for kNoAllocMaxFrames frames.
@@ -153,6 +165,8 @@ hipError_t launch_tiled(int unroll, int defer, int dtmask, int blocks, const Per
 // Workgroups a launch_tiled call with this many `blocks` actually launches.
 int launch_workgroups(int dtmask, const PersistentArgs& args, int blocks);
 hipError_t launch_plain(int dtype, const PlainArgs& args, hipStream_t stream);
+// One image whose escape is absorbing, one thread per pixel, tests in blocks.
+hipError_t launch_small(int dtype, const SmallArgs& args, hipStream_t stream);
 
 // One thread per pixel over the frame table (tiles of 16 x 16, one workgroup each).
 hipError_t launch_plain_batch(int dtmask, const PersistentArgs& args, hipStream_t stream);

@@ -270,13 +270,16 @@ bool absorbing(const jr_frame& f) {
 // round-to-nearest is odd).  On a window about 0 the pixel centres of (i, j) and
 // (W - 1 - i, H - 1 - j) are exact negatives, so the image is its own 180-degree
 // rotation and half of its rows give the rest.  The rows must be a band about the
-// middle.  Only the rows kernel stores mirrored pixels, and a tile must hold an
-// even number of rows: it then takes half as many and their mirror images, so a
-// frame has as many tiles, each of as many pixels, as without.
+// middle.  In the rows kernel a tile must hold an even number of rows: it then
+// takes half as many and their mirror images, so a frame has as many tiles, each
+// of as many pixels, as without.
+bool symmetric(const jr_frame& f) {
+    return f.mode == JR_JULIA && !(f.degree & 1) && 0.5 * (f.w.re_min + f.w.re_max) == 0.0 &&
+           0.5 * (f.w.im_min + f.w.im_max) == 0.0;
+}
+
 bool mirrors(const jr_frame& f, const jr_schedule& s) {
-    if (s.kernel != JR_KERNEL_ROWS || f.mode != JR_JULIA || (f.degree & 1)) return false;
-    if (0.5 * (f.w.re_min + f.w.re_max) != 0.0 || 0.5 * (f.w.im_min + f.w.im_max) != 0.0)
-        return false;
+    if (s.kernel != JR_KERNEL_ROWS || !symmetric(f)) return false;
     const int32_t rend = f.row_end == 0 ? f.height : f.row_end;
     const int32_t rows = rend - f.row_begin;
     return f.row_begin == f.height - rend && rows > 1 && (s.tile_h >= rows || s.tile_h % 2 == 0);
@@ -329,21 +332,21 @@ int64_t tile_count(const DevFrame& d) {
     return (int64_t)d.tiles_x * ((d.row_end - d.row_begin + d.tile_h - 1) / d.tile_h);
 }
 
-// Whether a launch looks for the traps of frames like f (find_trap): the rows
-// kernel ends orbits in them.  The search takes the host about 2 us where the
-// critical orbit is bounded (100 ns where it escapes at once), which an image
-// of fewer pixels or a lower cap does not win back.
-bool looks_for_trap(const jr_frame& f, const jr_schedule& s) {
-    return s.kernel == JR_KERNEL_ROWS && f.mode == JR_JULIA && f.map == JR_MAP_POLY &&
-           f.max_iter >= 32 && (int64_t)f.width * f.height >= 16384 && absorbing(f);
+// Whether the rows and single-image kernels look for the trap of a frame like f
+// (find_trap).  The search takes the host about 2 us where the critical orbit is
+// bounded (1 us where it escapes at once), which an image of fewer pixels and a
+// low cap, or of the lowest caps, does not win back.
+bool looks_for_trap(const jr_frame& f) {
+    return f.mode == JR_JULIA && f.map == JR_MAP_POLY && f.max_iter >= 32 &&
+           (f.max_iter > 128 || (int64_t)f.width * f.height >= 16384) && absorbing(f);
 }
 
 // Whether orbits of a frame without a trap are looked at for repeated iterates.
 // They come once an orbit has converged to its cycle as far as the arithmetic
 // can tell, 24 or 53 bits: about 24 or 53 iterations at a multiplier of 1/2 an
 // iteration, so lower caps do not win the look's cost back (under 2% of a drain).
-bool looks_for_repeats(const jr_frame& f, const jr_schedule& s) {
-    return s.kernel == JR_KERNEL_ROWS && f.max_iter > (f.dtype == JR_FP32 ? 128 : 256);
+bool looks_for_repeats(const jr_frame& f) {
+    return f.max_iter > (f.dtype == JR_FP32 ? 128 : 256);
 }
 
 // The device record of frame f (but for its first tile and its index); returns
@@ -385,7 +388,8 @@ double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d) {
     }
     d.tiles_x = (f.width + d.tile_w - 1) / d.tile_w;
     double steps = 256.0;
-    if (looks_for_trap(f, s)) {
+    const bool ends = s.kernel == JR_KERNEL_ROWS;
+    if (ends && looks_for_trap(f)) {
         // The critical orbit also says which of a batch's frames run long: one
         // that escapes after k steps leaves few orbits that run much longer,
         // and orbits in a trap end soon after they reach it.
@@ -393,9 +397,9 @@ double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d) {
         d.trap_p = jr::find_trap(f.c.re, f.c.im, d.degree, &d.trap_x, &d.trap_y, &d.trap_r,
                                  &d.trap_r1, &critical);
         steps = d.trap_p > 0 ? 16.0 : std::min(critical, 256);
-        if (d.trap_p == 0 && critical == jr::kCriticalSteps && looks_for_repeats(f, s))
+        if (d.trap_p == 0 && critical == jr::kCriticalSteps && looks_for_repeats(f))
             d.trap_p = -1;
-    } else if (looks_for_repeats(f, s)) {
+    } else if (ends && looks_for_repeats(f)) {
         d.trap_p = -1;
     }
     return frame_cost(f, steps) * (d.mirror ? 0.5 : 1.0);
@@ -718,8 +722,50 @@ jr_frame single_frame(jr_complex c, jr_window w, int32_t W, int32_t H, int32_t m
     return f;
 }
 
-int render_plain(jr_complex c, jr_window w, int32_t W, int32_t H, int32_t max_iter,
-                 int32_t dtype, int32_t mode, int32_t* out, void* stream, const char* who);
+// One image with one thread per pixel (jr_small), `f` checked: half the pixels
+// where the image is its own rotation, orbits ended in traps or where they repeat.
+int render_small(const jr_frame& f, int32_t* out, hipStream_t stream,
+                 const uint32_t* palette = nullptr, int32_t palette_len = 0) {
+    int dev;
+    DeviceInfo info;
+    int rc = current_device(&dev, &info);
+    if (rc) return rc;
+    jr::SmallArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.p.out = out;
+    a.p.hx = (f.w.re_max - f.w.re_min) / (2.0 * (double)f.width);
+    a.p.hy = (f.w.im_max - f.w.im_min) / (2.0 * (double)f.height);
+    a.p.cx = 0.5 * (f.w.re_min + f.w.re_max);
+    a.p.cy = 0.5 * (f.w.im_min + f.w.im_max);
+    a.p.cr = f.mode == JR_JULIA ? f.c.re : 0.0;
+    a.p.ci = f.mode == JR_JULIA ? f.c.im : 0.0;
+    a.p.W = f.width;
+    a.p.H = f.height;
+    a.p.max_iter = f.max_iter;
+    a.p.mode = f.mode;
+    a.mirror = symmetric(f) ? 1 : 0;
+    a.rows = a.mirror ? f.height - f.height / 2 : f.height;
+    a.palette = palette;
+    a.palette_len = palette_len;
+    bool bounded = f.mode == JR_MANDELBROT;  // orbits without a trap may be
+    if (looks_for_trap(f)) {
+        float x, y, r, r1;
+        int critical;
+        const int p = jr::find_trap(f.c.re, f.c.im, 2, &x, &y, &r, &r1, &critical);
+        if (p > 0 && p <= jr::kSmallDiscs) {
+            a.ends = p;
+            for (int k = 0; k < p; ++k)
+                jr::next_disc(p, 2, (float)f.c.re, (float)f.c.im, x, y, r, r1, a.x[k], a.y[k],
+                              a.r2[k]);
+        }
+        bounded = p > 0 || critical == jr::kCriticalSteps;
+    }
+    if (a.ends == 0 && bounded && looks_for_repeats(f)) a.ends = -1;
+    if (!absorbing(f)) a.ends = -2;
+    hipError_t e = jr::launch_small(f.dtype, a, stream);
+    if (e != hipSuccess) return hip_fail(e, "kernel launch");
+    return JR_OK;
+}
 
 int render_one(jr_complex c, jr_window w, int32_t W, int32_t H, int32_t max_iter, int32_t dtype,
                int32_t mode, int32_t* out, void* stream, const char* who) {
@@ -727,10 +773,9 @@ int render_one(jr_complex c, jr_window w, int32_t W, int32_t H, int32_t max_iter
     if (rc) return rc;
     if ((rc = check_out(out, who))) return rc;
     jr_schedule s = image_schedule(dtype, max_iter, (int64_t)W * H);
-    // one image on the one-thread-per-pixel kernel: its 2-D grid form
-    if (s.kernel == JR_KERNEL_PLAIN) return render_plain(c, w, W, H, max_iter, dtype, mode, out,
-                                                         stream, who);
     jr_frame f = single_frame(c, w, W, H, max_iter, dtype, mode);
+    // one image with one thread per pixel
+    if (s.kernel == JR_KERNEL_PLAIN) return render_small(f, out, (hipStream_t)stream);
     return enqueue_batch(&f, 1, out, (int64_t)W * H, &s, (hipStream_t)stream);
 }
 
@@ -744,6 +789,9 @@ int render_one_colored(jr_complex c, jr_window w, int32_t W, int32_t H, int32_t 
     if ((rc = check_palette(palette, palette_len, true, who))) return rc;
     jr_frame f = single_frame(c, w, W, H, max_iter, dtype, JR_JULIA);
     jr_schedule s = image_schedule(dtype, max_iter, (int64_t)W * H);
+    if (s.kernel == JR_KERNEL_PLAIN)
+        return render_small(f, reinterpret_cast<int32_t*>(out), (hipStream_t)stream, palette,
+                            palette_len);
     return enqueue_batch(&f, 1, reinterpret_cast<int32_t*>(out), (int64_t)W * H, &s,
                          (hipStream_t)stream, palette, palette_len);
 }
@@ -817,9 +865,10 @@ jr::CardioidArgs cardioid_args(const jr_cardioid_path& p, const jr_schedule& s, 
     f.out_offset = p.out_offset;
     const double cost = fill_frame(f, s, g.tmpl);
     const int64_t tiles = tile_count(g.tmpl);
+    const bool ends = s.kernel == JR_KERNEL_ROWS;
     g.tmpl.defer = 1;  // every |C_k| < 1.9 (check_cardioid): escape is absorbing
-    g.tmpl.trap_p = looks_for_repeats(f, s) ? -1 : 0;  // where a bounded orbit has no trap
-    g.traps = looks_for_trap(f, s) ? 1 : 0;
+    g.tmpl.trap_p = ends && looks_for_repeats(f) ? -1 : 0;  // where a bounded orbit has no trap
+    g.traps = ends && looks_for_trap(f) ? 1 : 0;
     g.dst = dst;
     g.step_re = p.step.re;
     g.step_im = p.step.im;

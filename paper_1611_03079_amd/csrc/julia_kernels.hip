@@ -495,6 +495,114 @@ __global__ __launch_bounds__(256) void jr_plain(PlainArgs p) {
 }
 
 // ---------------------------------------------------------------------------
+// One orbit per lane, no exchange between lanes: blocks of 16x4 pixels.
+// ---------------------------------------------------------------------------
+// A wave runs its 64 pixels in trips of four tests without a branch (one test
+// where an iteration costs many times the branch that follows it) until none is
+// left.  How an orbit may end before its escape or its cap:
+enum { kEndsNone = 0,      // not at all
+       kEndsTrap = 1,      // in a disc of the frame's trap
+       kEndsRepeat = 2,    // at an iterate that it has been at
+       kEndsExact = 3 };   // the same, and a pixel's first failed test ends its
+                           // count (escape may not be absorbing)
+struct Discs {
+    int n;
+    float x[kSmallDiscs], y[kSmallDiscs], r2[kSmallDiscs];
+};
+
+// The count of the pixel that starts at z.  There is no list to fill and drain, no
+// survivor waits for a tile's others, and a wave is never longer than one orbit,
+// which suits one image; a batch, whose tiles fill the chip to its end, loses by it
+// what a wave's 63 other lanes wait for the longest (over a table of frames: 64 FP64
+// frames 293 us against the rows kernel's 222, an uneven batch 2.96 ms against 1.79).
+template <class A, int ENDS>
+__device__ __forceinline__ int pixel_count(typename A::Z z, const typename A::C& c, int deg,
+                                           int max_iter, const Discs& discs) {
+    constexpr bool kEach = A::kRational || sizeof(typename A::V) == 8 && !std::is_same<A, ArF64>::value;
+    typename A::Z zs = z;  // an earlier iterate of the same orbit
+    int lead = 0, save = 8;
+    bool in = true, caught = false;
+    auto trip = [&]() {  // four tests and steps; whether any orbit goes on
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            in = A::check_step(z, c, deg) && (ENDS != kEndsExact || in);
+            lead += in ? 1 : 0;
+            if (kEach && u < 3 && __ballot(in && !caught) == 0) return false;
+        }
+        if (ENDS == kEndsTrap) {
+#pragma unroll
+            for (int k = 0; k < kSmallDiscs; ++k) {
+                if (k >= discs.n) break;
+                const float dx = A::lead(z.x) - discs.x[k], dy = A::lead(z.y) - discs.y[k];
+                caught |= in && __builtin_fmaf(dx, dx, dy * dy) < discs.r2[k];
+            }
+        }
+        return __ballot(in && !caught) != 0;
+    };
+#pragma unroll 1
+    for (int n = 0; n < max_iter; n += 8) {
+        if (!trip() || !trip()) break;
+        if (ENDS >= kEndsRepeat) {
+            caught |= in && A::same(z, zs);
+            if (n + 8 >= save) {  // windows that double meet every period
+                zs = z;
+                save *= 2;
+            }
+        }
+    }
+    return caught ? max_iter : min(lead, max_iter);
+}
+
+// ---------------------------------------------------------------------------
+// Single images.
+// ---------------------------------------------------------------------------
+// An image of a few thousand pixels has less than a wave per SIMD, and what
+// costs is the chain of one long orbit: the plain kernel's loop, with a branch
+// and the masks around it on every test, takes 240 cycles an iteration there.
+// Trips of four tests take the arithmetic's own latency.  A larger image is still
+// too small to spread the rows kernel's tiles evenly (a tile of long orbits
+// outlasts the rest).  Against what ran before: 100x100, FP64, cap 100: 9.7 -> 4.5
+// us a call (an empty kernel takes 3.9); 2000x2000, cap 100, against the rows
+// kernel: FP32 22 -> 14.5, FP64 41 -> 24.5, float-float 130 -> 70 us; 4096x4096:
+// FP32 41 -> 33, FP64 64 -> 47.
+template <class A, int ENDS, int COLOR>
+__global__ __launch_bounds__(64) void jr_small(SmallArgs s) {
+    const PlainArgs& p = s.p;
+    const int lane = (int)threadIdx.x;
+    Discs discs;
+    if (ENDS == kEndsTrap) {
+        discs.n = s.ends;
+#pragma unroll
+        for (int k = 0; k < kSmallDiscs; ++k) {
+            discs.x[k] = s.x[k];
+            discs.y[k] = s.y[k];
+            discs.r2[k] = s.r2[k];
+        }
+    }
+    // threads beyond the image repeat its last column or row and its stores
+    const int i = min((int)blockIdx.x * 16 + (lane & 15), p.W - 1);
+    for (int j0 = (int)blockIdx.y * 4; j0 < s.rows; j0 += (int)gridDim.y * 4) {
+        const int j = min(j0 + (lane >> 4), s.rows - 1);
+        const double px = pixel_re(p.cx, p.hx, i, p.W);
+        const double py = pixel_im(p.cy, p.hy, j, p.H);
+        typename A::Z z;
+        typename A::C c;
+        if (p.mode == kModeMandelbrot) {
+            z = A::make(A::coord(0.0), A::coord(0.0));
+            c = A::cmake(A::coord(px), A::coord(py));
+        } else {
+            z = A::make(A::coord(px), A::coord(py));
+            c = A::cmake(A::coord(p.cr), A::coord(p.ci));
+        }
+        int32_t v = pixel_count<A, ENDS>(z, c, 2, p.max_iter, discs);
+        if (COLOR) v = (int32_t)s.palette[min(v, s.palette_len - 1)];
+        const int64_t at = (int64_t)j * p.W + i;
+        p.out[at] = v;
+        if (s.mirror) p.out[(int64_t)p.H * p.W - 1 - at] = v;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Tiled kernel: waves stream pixels from tiles with lane refill.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
@@ -1320,41 +1428,24 @@ __device__ __forceinline__ void rows_tile(const Args& a, CFrame& F, int64_t t, i
     uint16_t* pos = (uint16_t*)(list + ZW * cap);
 
     // The frame's trap (find_trap): lane k holds disc k, the centre and the
-    // squared radius, which 1% + 1e-5 keeps inside the true disc whatever
-    // binary32 did to the centre and to the test itself (a centre's error
-    // grows along the cycle no faster than the radii do, so it stays within
-    // 16 * 2e-7 / 0.004 of the radius).  A bounded orbit then costs the few
-    // iterations that bring it into a disc and not the cap: an uneven batch
-    // (96 frames, sides 256..4096, caps 100..2000, FP32 and float-float) went
-    // from 54.8 ms on the refill stream to 2.65 ms.
+    // squared radius.  A bounded orbit then costs the few iterations that bring
+    // it into a disc and not the cap: an uneven batch (96 frames, sides
+    // 256..4096, caps 100..2000, FP32 and float-float) went from 54.8 ms on the
+    // refill stream to 2.65 ms.
     constexpr bool kTraps = !A::kRational && !MANDEL && K != 1;
     const int tp = K > 1 ? __builtin_amdgcn_readfirstlane(F.trap_p) : 0;
     float tcx = 0.0f, tcy = 0.0f, tr2 = -1.0f;
     if (kTraps && tp > 0) {
-        float x = F.trap_x, y = F.trap_y, rad = F.trap_r;
-        const float fcr = (float)F.cr, fci = (float)F.ci;
+        float x = F.trap_x, y = F.trap_y, r = F.trap_r;
 #pragma unroll 1
         for (int k = 0; k < tp; ++k) {
-            const float rt = rad * 0.99f - 1e-5f;
-            tcx = lane == k ? x : tcx;
-            tcy = lane == k ? y : tcy;
-            tr2 = lane == k ? rt * rt : tr2;
-            const float m = __builtin_sqrtf(x * x + y * y);
-            float wr = x, wi = y, p0 = m, p1 = m + rad;
-#pragma unroll 1
-            for (int d = 1; d < deg; ++d) {
-                const float t = wr * x - wi * y;
-                wi = wr * y + wi * x;
-                wr = t;
-                p0 *= m;
-                p1 *= m + rad;
-            }
-            x = wr + fcr;
-            y = wi + fci;
-            rad = tp == 2 ? F.trap_r1 : p1 - p0;
+            float dx, dy, r2;
+            next_disc(tp, deg, (float)F.cr, (float)F.ci, x, y, r, F.trap_r1, dx, dy, r2);
+            tcx = lane == k ? dx : tcx;
+            tcy = lane == k ? dy : tcy;
+            tr2 = lane == k ? r2 : tr2;
         }
     }
-
     auto disc_of = [&](int k, float& cx, float& cy, float& r2) {
         cx = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(tcx), k));
         cy = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(tcy), k));
@@ -2204,6 +2295,45 @@ hipError_t launch_plain(int dtype, const PlainArgs& args, hipStream_t stream) {
         case kFP64: hipLaunchKernelGGL(jr_plain<ArF64>, grid, dim3(256), 0, stream, args); break;
         case kFP32: hipLaunchKernelGGL(jr_plain<ArF32>, grid, dim3(256), 0, stream, args); break;
         case kFF: hipLaunchKernelGGL(jr_plain<ArFF>, grid, dim3(256), 0, stream, args); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+template <class A>
+static void launch_small_as(dim3 grid, const SmallArgs& a, hipStream_t stream) {
+    auto go = [&](auto ends) {
+        constexpr int E = decltype(ends)::value;
+        if (a.palette_len > 0)
+            hipLaunchKernelGGL((jr_small<A, E, 1>), grid, dim3(64), 0, stream, a);
+        else
+            hipLaunchKernelGGL((jr_small<A, E, 0>), grid, dim3(64), 0, stream, a);
+    };
+    if (a.ends > 0)
+        go(std::integral_constant<int, kEndsTrap>());
+    else if (a.ends == -1)
+        go(std::integral_constant<int, kEndsRepeat>());
+    else if (a.ends == -2)
+        go(std::integral_constant<int, kEndsExact>());
+    else
+        go(std::integral_constant<int, kEndsNone>());
+}
+
+hipError_t launch_small(int dtype, const SmallArgs& args, hipStream_t stream) {
+    const unsigned gx = (unsigned)((args.p.W + 15) / 16);
+    const int64_t rows4 = ((int64_t)args.rows + 3) / 4;
+    // Waves of a large image take several blocks each, spread over its height, and
+    // start up once for them: 4096^2 at cap 100, 131072 blocks, takes 46.7 us in
+    // 65536 waves and 55.2 in 131072 in FP64, 32.8 and 42.2 in FP32 (53.4 and 37.1
+    // in 16384, too few to even out).  Float-float blocks are long enough: 231 us
+    // in 131072, 255 in 65536.
+    const int64_t waves = dtype == kFF ? 131072 : 65536;
+    const int64_t most = waves / gx > 1 ? waves / gx : 1;
+    dim3 grid(gx, (unsigned)(rows4 < most ? rows4 : most));
+    switch (dtype) {
+        case kFP64: launch_small_as<ArF64>(grid, args, stream); break;
+        case kFP32: launch_small_as<ArF32>(grid, args, stream); break;
+        case kFF: launch_small_as<ArFF>(grid, args, stream); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -183,4 +183,30 @@ JR_HOST_DEVICE inline int find_trap(double cr, double ci, int degree, float* x, 
     return 0;
 }
 
+// A disc of a trap as a kernel tests it (centre and squared radius), and the step
+// from (x, y, r) to the next one.  1% + 1e-5 keeps it inside the true disc
+// whatever binary32 did to the centre and to the test itself (a centre's error
+// grows along the cycle no faster than the radii do, so it stays within
+// 16 * 2e-7 / 0.004 of the radius).
+JR_HOST_DEVICE inline void next_disc(int p, int degree, float cr, float ci, float& x, float& y,
+                                     float& r, float r1, float& disc_x, float& disc_y,
+                                     float& disc_r2) {
+    const float rt = r * 0.99f - 1e-5f;
+    disc_x = x;
+    disc_y = y;
+    disc_r2 = rt * rt;
+    const float m = sqrtf(x * x + y * y);
+    float wr = x, wi = y, p0 = m, p1 = m + r;
+    for (int d = 1; d < degree; ++d) {
+        const float t = wr * x - wi * y;
+        wi = wr * y + wi * x;
+        wr = t;
+        p0 *= m;
+        p1 *= m + r;
+    }
+    x = wr + cr;
+    y = wi + ci;
+    r = p == 2 ? r1 : p1 - p0;
+}
+
 }  // namespace jr
