@@ -34,7 +34,8 @@ struct alignas(16) DevFrame {
     int32_t max_iter;
     int32_t dtype;           // kFP64 / kFP32 / kFF
     int32_t mode;            // kModeJulia / kModeMandelbrot
-    int32_t defer;           // 1: escape absorbing over the whole frame
+    int32_t defer;           // 1: escape absorbing over the whole frame; 0: not known to
+                             // be; -1 (FP64, rows kernel): as 0, everywhere
     int32_t row_begin, row_end;
     int32_t tiles_x;         // tiles per tile row of this frame
     int32_t tile_w, tile_h;
@@ -124,6 +125,7 @@ struct SmallArgs {
     int32_t rows, mirror;  // rows computed; 1: counts go to the opposite pixels too
     int32_t ends;          // > 0: number of trap discs; -1: orbits end where they repeat;
                            // -2: the same, and escape may not be absorbing; 0: neither
+    int32_t scaled;        // FP64: the form on twice the iterate may be used
     int32_t palette_len;   // > 0: stores palette[min(count, palette_len - 1)]
     const uint32_t* palette;
     float x[kSmallDiscs], y[kSmallDiscs], r2[kSmallDiscs];

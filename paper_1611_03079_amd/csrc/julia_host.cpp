@@ -285,6 +285,18 @@ bool mirrors(const jr_frame& f, const jr_schedule& s) {
     return f.row_begin == f.height - rend && rows > 1 && (s.tile_h >= rows || s.tile_h % 2 == 0);
 }
 
+// Whether no part of an FP64 frame's constant and window lies strictly between 0
+// and 2^-200, so that its iteration may run on twice the iterate (ArF64S).
+bool scales(const jr_frame& f) {
+    const double hx = (f.w.re_max - f.w.re_min) / (2.0 * f.width);
+    const double hy = (f.w.im_max - f.w.im_min) / (2.0 * f.height);
+    const double parts[6] = {hx, hy, 0.5 * (f.w.re_min + f.w.re_max),
+                             0.5 * (f.w.im_min + f.w.im_max),
+                             f.mode == JR_JULIA ? f.c.re : 0.0, f.mode == JR_JULIA ? f.c.im : 0.0};
+    return std::none_of(parts, parts + 6,
+                        [](double v) { return v != 0.0 && std::fabs(v) < std::ldexp(1.0, -200); });
+}
+
 // Totals of a frame table, for the launch shape and the kernel variant.
 struct TableStats {
     int64_t total_tiles = 0;
@@ -366,8 +378,11 @@ double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d) {
     d.max_iter = f.max_iter;
     d.dtype = f.dtype;
     d.mode = f.mode;
-    d.defer = absorbing(f) ? 1 : 0;
     d.degree = f.degree == 0 ? 2 : f.degree;
+    d.defer = absorbing(f) ? 1 : 0;
+    if (s.kernel == JR_KERNEL_ROWS && f.dtype == JR_FP64 && f.map == JR_MAP_POLY &&
+        d.degree == 2 && !scales(f))
+        d.defer = -1;
     d.map = f.map;
     d.lr = f.map == JR_MAP_RATIONAL ? f.lambda.re : 0.0;
     d.li = f.map == JR_MAP_RATIONAL ? f.lambda.im : 0.0;
@@ -743,6 +758,7 @@ int render_small(const jr_frame& f, int32_t* out, hipStream_t stream,
     a.p.H = f.height;
     a.p.max_iter = f.max_iter;
     a.p.mode = f.mode;
+    a.scaled = f.dtype == JR_FP64 && scales(f) ? 1 : 0;
     a.mirror = symmetric(f) ? 1 : 0;
     a.rows = a.mirror ? f.height - f.height / 2 : f.height;
     a.palette = palette;
@@ -866,7 +882,7 @@ jr::CardioidArgs cardioid_args(const jr_cardioid_path& p, const jr_schedule& s, 
     const double cost = fill_frame(f, s, g.tmpl);
     const int64_t tiles = tile_count(g.tmpl);
     const bool ends = s.kernel == JR_KERNEL_ROWS;
-    g.tmpl.defer = 1;  // every |C_k| < 1.9 (check_cardioid): escape is absorbing
+    if (g.tmpl.defer == 0) g.tmpl.defer = 1;  // every |C_k| < 1.9 (check_cardioid): escape is absorbing
     g.tmpl.trap_p = ends && looks_for_repeats(f) ? -1 : 0;  // where a bounded orbit has no trap
     g.traps = ends && looks_for_trap(f) ? 1 : 0;
     g.dst = dst;

@@ -89,6 +89,54 @@ struct ArF64 {
     }
 };
 
+// The same iteration on X = 2x, Y = 2y and 2C: X' = fma(1/2, X^2 - Y^2, 2 Re C)
+// and Y' = X Y + 2 Im C are twice x' and y' as rounded above, bit for bit, and
+// X^2 + Y^2 <= 16 is the same test, since scaling by a power of two commutes with
+// rounding.  Eight binary64 operations where the plain form takes nine (2x and the
+// sum with Re C become one fma with it); binary64 operations are what bounds
+// FP64 launches (0.96 a cycle and CU).  Near underflow it does not hold: there a
+// scaled value keeps bits that the plain one loses.  The host therefore gives
+// this form only frames (DevFrame::defer 1) whose constants and window have no
+// part between 0 and 2^-200; then a product that underflows is added to a part of
+// C that swallows it, or, where that part is 0, belongs to an orbit on an axis
+// that has shrunk by hundreds of binary orders and stays bounded.
+struct ArF64S {
+    static constexpr bool kRational = false;
+    struct Z { double x, y; };
+    struct C { double r, i; };
+    using V = double;
+    __device__ static V coord(double v) { return v + v; }
+    __device__ static float lead(V v) { return (float)v * 0.5f; }
+    __device__ static V shfl(V v, int src) { return __shfl(v, src); }
+    __device__ static Z make(V x, V y) { return Z{x, y}; }
+    __device__ static bool same(const Z& a, const Z& b) { return a.x == b.x && a.y == b.y; }
+    __device__ static V nowhere() { return __builtin_nan(""); }
+    __device__ static C cmake(V r, V i) { return C{r, i}; }
+    __device__ static bool inside(const Z& z, const C&, int) {
+        double x2 = z.x * z.x;
+        double y2 = z.y * z.y;
+        return x2 + y2 <= 16.0;
+    }
+    __device__ static void step(Z& z, const C& c, int) {
+        double x2 = z.x * z.x;
+        double y2 = z.y * z.y;
+        double re = x2 - y2;
+        double im = z.x * z.y;
+        z.x = __builtin_fma(re, 0.5, c.r);
+        z.y = im + c.i;
+    }
+    __device__ static bool check_step(Z& z, const C& c, int) {
+        double x2 = z.x * z.x;
+        double y2 = z.y * z.y;
+        bool ok = (x2 + y2 <= 16.0);
+        double re = x2 - y2;
+        double im = z.x * z.y;
+        z.x = __builtin_fma(re, 0.5, c.r);
+        z.y = im + c.i;
+        return ok;
+    }
+};
+
 // FP32: with t = fma(x, x, cr) = x^2 + Re C, the escape test is
 // fma(y, y, t) > lim, lim = fl(4 + cr) (both sides carry Re C), and the update
 // x' = fma(-y, y, t), y' = fma(x + x, y, ci): the test shares t with the
@@ -514,11 +562,11 @@ struct Discs {
 // survivor waits for a tile's others, and a wave is never longer than one orbit,
 // which suits one image; a batch, whose tiles fill the chip to its end, loses by it
 // what a wave's 63 other lanes wait for the longest (over a table of frames: 64 FP64
-// frames 293 us against the rows kernel's 222, an uneven batch 2.96 ms against 1.79).
+// frames 270 us against the rows kernel's 222, an uneven batch 2.51 ms against 1.79).
 template <class A, int ENDS>
 __device__ __forceinline__ int pixel_count(typename A::Z z, const typename A::C& c, int deg,
                                            int max_iter, const Discs& discs) {
-    constexpr bool kEach = A::kRational || sizeof(typename A::V) == 8 && !std::is_same<A, ArF64>::value;
+    constexpr bool kEach = std::is_same<A, ArFF>::value;
     typename A::Z zs = z;  // an earlier iterate of the same orbit
     int lead = 0, save = 8;
     bool in = true, caught = false;
@@ -1702,7 +1750,8 @@ __device__ __forceinline__ void rows_tile(const Args& a, CFrame& F, int64_t t, i
     // resident waves).  FP32 takes four rows at a time where its list holds
     // eight rows' survivors (FP32-only kernels), two otherwise, as FP64
     // does: a drain should find several groups' survivors waiting.
-    constexpr bool kGroups = std::is_same<A, ArF32>::value || std::is_same<A, ArF64>::value;
+    constexpr bool kGroups = std::is_same<A, ArF32>::value || std::is_same<A, ArF64>::value ||
+                             std::is_same<A, ArF64S>::value;
     constexpr int G = (std::is_same<A, ArF32>::value && LROWS >= 2 * kGroupFP32) ? kGroupFP32 : 2;
     static_assert(2 * G <= LROWS, "the list holds at least two groups' survivors");
     if (K != 1 && kGroups) {
@@ -1748,7 +1797,7 @@ __device__ __forceinline__ void rows_tile(const Args& a, CFrame& F, int64_t t, i
             // group has escaped (light regions escape within a test or two;
             // no pixel survives, so `done` need not be a multiple of 4).  The
             // same early end made FP32 groups slower and is left out there.
-            constexpr bool kEarly = std::is_same<A, ArF64>::value;
+            constexpr bool kEarly = sizeof(typename A::V) == 8;
             auto first_trip = [&]() {
                 if constexpr (kEarly) {
 #pragma unroll
@@ -1872,10 +1921,10 @@ __global__ __launch_bounds__(64 * WPB) void jr_rows(PersistentArgs a) {
     auto tile = [&](int64_t t) {
         CFrame& F = frames[frame_of_tile(frames, a.nframes, t, a.frames_per_tile)];
         const bool mandel = F.mode == kModeMandelbrot;
-        bool absorbs = F.defer != 0;
+        bool absorbs = F.defer > 0;
         // A Mandelbrot window that reaches beyond |C| = 1.9 (any view of the whole
         // set) has most of its tiles within.
-        if (!absorbs && mandel) absorbs = tile_absorbs(F, t);
+        if (F.defer == 0 && mandel) absorbs = tile_absorbs(F, t);
         const bool abs = absorbs;
         // The first block's length: the schedule's, rounded up to a multiple
         // of 4 (four iterations per trip), or 1 where escape may not be
@@ -1895,13 +1944,15 @@ __global__ __launch_bounds__(64 * WPB) void jr_rows(PersistentArgs a) {
         else                                                                                \
             rows_tile<A_, K_, M_, COLOR, S::rows, D_>(a, F, t, P, list, done_at);           \
     } while (0)
-#define JR_ROWS(A_)                                \
+        // S_: the form of the arithmetic for blocks
+#define JR_ROWS2(S_, A_)                           \
     do {                                           \
-        if (abs && !mandel) JR_ROWS_(A_, K, 0, DD); \
-        else if (abs) JR_ROWS_(A_, K, 1, DD);       \
+        if (abs && !mandel) JR_ROWS_(S_, K, 0, DD); \
+        else if (abs) JR_ROWS_(S_, K, 1, DD);       \
         else if (!mandel) JR_ROWS_(A_, 1, 0, 0);    \
         else JR_ROWS_(A_, 1, 1, 0);                 \
     } while (0)
+#define JR_ROWS(A_) JR_ROWS2(A_, A_)
         // rational maps: Julia images in FP64 or FP32 (the host checks)
 #define JR_ROWS_R(A_)                  \
     do {                               \
@@ -1933,13 +1984,14 @@ __global__ __launch_bounds__(64 * WPB) void jr_rows(PersistentArgs a) {
                 if (F.dtype == kFP32) JR_ROWS(ArF32);
             }
             if constexpr (k64) {
-                if (F.dtype == kFP64) JR_ROWS(ArF64);
+                if (F.dtype == kFP64) JR_ROWS2(ArF64S, ArF64);
             }
             if constexpr (kff) {
                 if (F.dtype == kFF) JR_ROWS(ArFF);
             }
         }
 #undef JR_ROWS
+#undef JR_ROWS2
 #undef JR_ROWS_R
 #undef JR_ROWS_
     };
@@ -2331,7 +2383,12 @@ hipError_t launch_small(int dtype, const SmallArgs& args, hipStream_t stream) {
     const int64_t most = waves / gx > 1 ? waves / gx : 1;
     dim3 grid(gx, (unsigned)(rows4 < most ? rows4 : most));
     switch (dtype) {
-        case kFP64: launch_small_as<ArF64>(grid, args, stream); break;
+        case kFP64:
+            if (args.scaled)
+                launch_small_as<ArF64S>(grid, args, stream);
+            else
+                launch_small_as<ArF64>(grid, args, stream);
+            break;
         case kFP32: launch_small_as<ArF32>(grid, args, stream); break;
         case kFF: launch_small_as<ArFF>(grid, args, stream); break;
         default: return hipErrorInvalidValue;
