@@ -285,15 +285,18 @@ bool mirrors(const jr_frame& f, const jr_schedule& s) {
     return f.row_begin == f.height - rend && rows > 1 && (s.tile_h >= rows || s.tile_h % 2 == 0);
 }
 
-// Whether no part of an FP64 frame's constant and window lies strictly between 0
-// and 2^-200, so that its iteration may run on twice the iterate (ArF64S).
+// Whether no part of an FP64 frame's constants and window lies strictly between 0
+// and 2^-200, so that its iteration may run on twice the iterate (ArF64S) or with
+// a shared reciprocal (ArF64RS).
 bool scales(const jr_frame& f) {
     const double hx = (f.w.re_max - f.w.re_min) / (2.0 * f.width);
     const double hy = (f.w.im_max - f.w.im_min) / (2.0 * f.height);
-    const double parts[6] = {hx, hy, 0.5 * (f.w.re_min + f.w.re_max),
+    const bool julia = f.mode == JR_JULIA, rational = f.map == JR_MAP_RATIONAL;
+    const double parts[8] = {hx, hy, 0.5 * (f.w.re_min + f.w.re_max),
                              0.5 * (f.w.im_min + f.w.im_max),
-                             f.mode == JR_JULIA ? f.c.re : 0.0, f.mode == JR_JULIA ? f.c.im : 0.0};
-    return std::none_of(parts, parts + 6,
+                             julia ? f.c.re : 0.0, julia ? f.c.im : 0.0,
+                             rational ? f.lambda.re : 0.0, rational ? f.lambda.im : 0.0};
+    return std::none_of(parts, parts + 8,
                         [](double v) { return v != 0.0 && std::fabs(v) < std::ldexp(1.0, -200); });
 }
 
@@ -380,8 +383,8 @@ double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d) {
     d.mode = f.mode;
     d.degree = f.degree == 0 ? 2 : f.degree;
     d.defer = absorbing(f) ? 1 : 0;
-    if (s.kernel == JR_KERNEL_ROWS && f.dtype == JR_FP64 && f.map == JR_MAP_POLY &&
-        d.degree == 2 && !scales(f))
+    if (s.kernel == JR_KERNEL_ROWS && f.dtype == JR_FP64 &&
+        (f.map == JR_MAP_RATIONAL || d.degree == 2) && !scales(f))
         d.defer = -1;
     d.map = f.map;
     d.lr = f.map == JR_MAP_RATIONAL ? f.lambda.re : 0.0;

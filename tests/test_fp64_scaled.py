@@ -5,6 +5,10 @@ On the CPU, numpy's counts of that form equal the oracle's over constants with
 zero, small and large parts and windows of every scale that it is given (no part
 strictly between 0 and 2^-200).  On the GPU, images of those frames and of frames
 it is not given equal the oracle's."""
+import math
+import random
+from fractions import Fraction
+
 import numpy as np
 import pytest
 
@@ -48,6 +52,60 @@ def test_the_scaled_form_counts_alike(win):
         np.testing.assert_array_equal(scaled_counts(c, win, 41, 30, 150, False), want, err_msg=str(c))
     want = oracle.render(0j, win, 41, 29, 150, "fp64", "mandelbrot")
     np.testing.assert_array_equal(scaled_counts(0j, win, 41, 29, 150, True), want)
+
+
+def test_a_shared_reciprocal_divides_correctly():
+    """From a reciprocal good to an ulp, one more step and one correction give
+    the rounded quotient, but for a divisor with every bit set (exact fma through
+    fractions)."""
+    def fma(a, b, c):
+        v = Fraction(a) * Fraction(b) + Fraction(c)
+        return v.numerator / v.denominator
+    rng = random.Random(1)
+    for k in range(6000):
+        m = rng.getrandbits(52)
+        if k % 8 == 0:
+            m = rng.choice([0, 1, 2, (1 << 52) - 2, (1 << 52) - 3, 1 << 51, (1 << 51) - 1])
+        q = math.ldexp((1 << 52) | m, rng.randint(-500, 16) - 52)
+        a = rng.uniform(-1, 1) * 2.0 ** rng.randint(-400, 8)
+        if m == (1 << 52) - 1:
+            continue
+        for off in (-1, 0, 1):
+            r = 1.0 / q
+            r += off * math.ulp(r)
+            r = fma(fma(-q, r, 1.0), r, r)
+            t = a * r
+            assert fma(fma(-q, t, a), r, t) == a / q
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("degree", [2, 3, 4, 8])
+def test_rational_quotients_equal_the_oracle(degree):
+    """Both quotients of the rational map come from one reciprocal: windows on the
+    pole (0, and the next to it), divisors from 2^16 down past 2^-500, divisors
+    that are powers of two and the like (exact orbits), real and imaginary
+    constants, and parts too small for the shared form, in every schedule of blocks."""
+    import torch
+    import paper_1611_03079_amd as jr
+    from workloads import Frame
+    rng = np.random.default_rng(degree)
+    wins = [(-1.6, 1.6, -1.2, 1.2), (-1.0, 1.0, -1.0, 1.0), (-1e-3, 1e-3, -1e-3, 1.1e-3),
+            (-1e-40, 1e-40, -1e-40, 2e-40), (-1e-90, 1e-90, -2e-90, 1e-90),
+            (-1e-300, 1e-300, -1, 1), (0.5, 0.5 + 2.0 ** -30, 0.25, 0.75)]
+    cases = [(0j, 0.25 + 0j), (-0.5 + 0j, -0.125 + 0j), (0.3j, 0.01j), (0.25 + 0.25j, 1e-30 + 0j),
+             (-0.1 + 0.1j, complex(2.0 ** -300, 0.0)), (complex(2.0 ** -260, 0.4), -0.01 + 0j)]
+    cases += [(complex(*rng.uniform(-0.7, 0.7, 2)), complex(*rng.uniform(-0.05, 0.05, 2)))
+              for _ in range(10)]
+    frames = [Frame(c, w, 37, 26, 70, "fp64", "julia", degree, lam) for c, lam in cases
+              for w in wins]
+    want = [oracle.render(f.c, f.window, 37, 26, 70, "fp64", "julia", degree, f.lam)
+            for f in frames]
+    for sched in (None, jr.Schedule(64, 8, 4, 0, 8, 0, 16, "cost", "rows", 8),
+                  jr.Schedule(20, 6, 8, 0, 16, 1, 16, "table", "rows", 4)):
+        _, views = jr.render_batch(frames, sched)
+        torch.cuda.synchronize()
+        for f, v, w in zip(frames, views, want):
+            np.testing.assert_array_equal(v.cpu().numpy(), w, err_msg=str(f))
 
 
 @pytest.mark.gpu
