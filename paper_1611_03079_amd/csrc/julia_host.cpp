@@ -173,9 +173,9 @@ std::mutex g_sched_mu;
 jr_schedule g_default[3] = {
     // tile_w, tile_h, unroll, defer, refill, persistent, waves_per_cu, order, kernel, bail,
     // handoff
-    {64, 16, 8, 0, 16, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 16, 32},  // FP64
-    {64, 8, 8, 0, 32, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 6, 0},     // FP32
-    {64, 16, 8, 0, 16, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 8, 0},    // FF
+    {64, 16, 8, 0, 16, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 8, 32},   // FP64
+    {64, 16, 8, 0, 16, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 16, 64},  // FP32
+    {64, 16, 8, 0, 8, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 8, 0},     // FF
 };
 
 bool g_default_set[3];  // replaced by jr_set_default_schedule
