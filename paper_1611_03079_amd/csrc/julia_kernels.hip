@@ -705,8 +705,9 @@ __global__ __launch_bounds__(64) void jr_small(SmallArgs s) {
     }
     // threads beyond the image repeat its last column or row and its stores
     const int i = min((int)blockIdx.x * 16 + (lane & 15), p.W - 1);
-    for (int j0 = (int)blockIdx.y * 4; j0 < s.rows; j0 += (int)gridDim.y * 4) {
-        const int j = min(j0 + (lane >> 4), s.rows - 1);
+    // unsigned: the step past the last of 2^31 - 1 rows does not wrap
+    for (unsigned j0 = blockIdx.y * 4; j0 < (unsigned)s.rows; j0 += gridDim.y * 4) {
+        const int j = (int)min(j0 + (unsigned)(lane >> 4), (unsigned)s.rows - 1u);
         const double px = pixel_re(p.cx, p.hx, i, p.W);
         const double py = pixel_im(p.cy, p.hy, j, p.H);
         typename A::Z z;
@@ -2488,7 +2489,7 @@ hipError_t launch_small(int dtype, const SmallArgs& args, hipStream_t stream) {
     // in 16384, too few to even out).  Float-float blocks are long enough: 231 us
     // in 131072, 255 in 65536.
     const int64_t waves = dtype == kFF ? 131072 : 65536;
-    const int64_t most = waves / gx > 1 ? waves / gx : 1;
+    const int64_t fit = waves / gx > 1 ? waves / gx : 1, most = fit < 65535 ? fit : 65535;
     dim3 grid(gx, (unsigned)(rows4 < most ? rows4 : most));
     switch (dtype) {
         case kFP64:

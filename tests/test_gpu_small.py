@@ -35,6 +35,17 @@ def test_small_images_equal_the_oracle(dtype):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["fp64", "fp32", "ff"])
+def test_narrow_tall_images(dtype):
+    """More blocks of rows than a grid's 65535: each takes several."""
+    for w, h, win in ((1, 300001, (-1.6, 1.5, -1.2, 1.25)), (17, 270003, (-1.6, 1.6, -1.2, 1.2))):
+        got = jr.render(complex(-0.4, 0.6), win, w, h, 20, dtype)
+        torch.cuda.synchronize()
+        want = oracle.render(complex(-0.4, 0.6), win, w, h, 20, dtype)
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.gpu
 def test_output_views():
     """Images land in the first elements of a larger tensor and of a slice."""
     c, win = complex(-0.8, 0.156), (-1.5, 1.5, -1.5, 1.5)
