@@ -769,7 +769,12 @@ def main():
                              "unit": "TFLOP/s", "frac": round(alu_tflops / PEAK_FP32_TFLOPS, 4),
                              "peak_unpacked": PEAK_FP32_UNPACKED_TFLOPS,
                              "frac_unpacked": round(alu_tflops / PEAK_FP32_UNPACKED_TFLOPS, 4),
-                             "flops_per_launch": FLOP_PER_ITER * iters},
+                             "flops_per_launch": FLOP_PER_ITER * iters,
+                             "flops_note": "8 x the delivered counts, not operations run: a "
+                                           "frame that is its own image under the half turn "
+                                           "has half of its orbits computed and each count "
+                                           "stored twice, and an orbit known to stay bounded "
+                                           "gets its cap without running to it"},
                      "kernel": kernel_instance(sched) + " (libjulia.so)"},
     }
     if not args.no_extra:

@@ -81,8 +81,8 @@ WALL_PIXELS = 1 << 16
 
 def time_singles(frames, schedule: jr.Schedule, reps: int = 3) -> float:
     """Sum over the frames of the time of each rendered on its own.  A single
-    image under a plain schedule runs the two-dimensional one-thread-per-pixel
-    kernel (julia_render_plain), which is what is timed for it.  Images below
+    image under a plain schedule runs the single-image form of the
+    one-thread-per-pixel kernel, which is what is timed for it.  Images below
     WALL_PIXELS are timed by time_render_wall."""
     if all(f.pixels < WALL_PIXELS for f in frames):
         return sum(time_render_wall(f, schedule, reps=reps) for f in frames)
@@ -101,31 +101,52 @@ def time_render_wall(f, schedule: jr.Schedule, reps: int = 3, calls: int = 50) -
 
     def one():
         jr.render(f.c, f.window, f.width, f.height, f.max_iter, f.dtype, out=out,
-                  plain=plain, schedule=None if plain else schedule, mode=f.mode,
-                  degree=f.degree)
+                  schedule=None if plain else schedule, mode=f.mode, degree=f.degree)
 
-    one()
-    torch.cuda.synchronize()
-    times = []
-    for _ in range(reps):
-        t0 = time.perf_counter()
-        for _ in range(calls):
-            one()
+    def wall():
+        one()
         torch.cuda.synchronize()
-        times.append((time.perf_counter() - t0) * 1e3 / calls)
-    times.sort()
-    return times[len(times) // 2]
+        times = []
+        for _ in range(reps):
+            t0 = time.perf_counter()
+            for _ in range(calls):
+                one()
+            torch.cuda.synchronize()
+            times.append((time.perf_counter() - t0) * 1e3 / calls)
+        times.sort()
+        return times[len(times) // 2]
+
+    return _as_image(f, schedule, wall) if plain else wall()
+
+
+def _as_image(f, schedule: jr.Schedule, timed):
+    """timed() while one-image calls of f's size run `schedule`: an entry on
+    the plain kernel takes the single-image form of it, which only they do.
+    Per-size schedules that were set before are dropped; the cached ones are
+    installed again by the next call that needs them."""
+    jr.lib.jr_clear_image_schedules()
+    jr._IMAGE_SCHEDULES_DONE = True
+    try:
+        jr.set_image_schedule(f.dtype, f.max_iter, f.width * f.height, schedule)
+        return timed()
+    finally:
+        jr.lib.jr_clear_image_schedules()
+        jr._IMAGE_SCHEDULES_DONE = False  # installed again by the next call
 
 
 def time_render_plain(f, reps: int = 3, span_ms: float = 5.0) -> float:
-    """Sustained device time (ms) per render of one frame by the plain kernel,
-    timed like time_plan."""
+    """Sustained device time (ms) per render of one frame with one thread per
+    pixel, as a one-image call runs it, timed like time_plan."""
+    return _as_image(f, jr.Schedule(kernel="plain"), lambda: _time_render(f, reps, span_ms))
+
+
+def _time_render(f, reps: int, span_ms: float) -> float:
     import torch
     out = torch.empty((f.height, f.width), dtype=torch.int32, device="cuda")
 
     def one():
-        jr.render(f.c, f.window, f.width, f.height, f.max_iter, f.dtype, out=out,
-                  plain=True, mode=f.mode, degree=f.degree)
+        jr.render(f.c, f.window, f.width, f.height, f.max_iter, f.dtype, out=out, mode=f.mode,
+                  degree=f.degree)
 
     one()
     torch.cuda.synchronize()
