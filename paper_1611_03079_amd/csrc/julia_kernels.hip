@@ -1693,6 +1693,12 @@ __device__ __forceinline__ void rows_tile(const Args& a, CFrame& F, int64_t t, i
     auto drain_as = [&](auto ends) {
         constexpr bool kTrapped = decltype(ends)::value == 1;
         constexpr bool kRepeats = decltype(ends)::value == 2;
+        // FP64 only, the type of deep views, whose bounded orbits take hundreds of
+        // iterations to repeat bit for bit: 24 zoom frames 3.47 -> 2.71 ms.  With
+        // float-float and FP32 too, an uneven batch of theirs, whose frames have
+        // traps, lost 2.8% to the code's registers; in jr_small, where windows
+        // double, a coloured view at cap 500 lost 4.8%.
+        constexpr bool kSettles = std::is_same<A, ArF64>::value || std::is_same<A, ArF64S>::value;
         // Other lanes read the entries written above, and the next rows
         // overwrite them afterwards: keep the compiler from moving LDS
         // accesses across either point (one wave runs them in order).
@@ -1729,7 +1735,17 @@ __device__ __forceinline__ void rows_tile(const Args& a, CFrame& F, int64_t t, i
         };
         for (;;) {
             if (kRepeats && --until == 0) {
-                const bool same = it && A::same(z, zw);
+                bool same = it && A::same(z, zw);
+                if constexpr (kSettles) {
+                    // near a cycle long before the first repeat; the windows are
+                    // even, so an orbit of period 2 is near itself too
+                    const float dx = A::lead(z.x) - A::lead(zw.x);
+                    const float dy = A::lead(z.y) - A::lead(zw.y);
+                    const bool near = it && dx * dx + dy * dy < 2e-3f;
+                    if (__ballot(near) != 0)
+                        same |= near && settles(A::lead(z.x), A::lead(z.y), A::lead(c.r),
+                                                A::lead(c.i));
+                }
                 cnt = same ? mi : cnt;
                 fi = fi || same;
                 it = it && !same;

@@ -209,4 +209,43 @@ JR_HOST_DEVICE inline void next_disc(int p, int degree, float cr, float ci, floa
     r = p == 2 ? r1 : p1 - p0;
 }
 
+#ifdef __HIP_DEVICE_COMPILE__
+__device__ inline float near_sqrt(float v) { return __builtin_amdgcn_sqrtf(v); }  // 1 ulp
+__device__ inline float near_reciprocal(float v) { return __builtin_amdgcn_rcpf(v); }
+#else
+JR_HOST_DEVICE inline float near_sqrt(float v) { return sqrtf(v); }
+JR_HOST_DEVICE inline float near_reciprocal(float v) { return 1.0f / v; }
+#endif
+
+// Whether the orbit of Z^2 + C that is at z (binary32 parts of the iterate and of
+// C) never escapes, for orbits whose frame has no trap, above all of Mandelbrot
+// pixels, each with a C of its own.  One Newton step from z looks for a point w
+// of a cycle of period 1 or 2, and a disc about w that two steps send into itself
+// and that holds z is a trap: |f(w + h) - f(w)| <= 2 |w| |h| + |h|^2, twice.  eps =
+// 2e-5 covers the rounding of one step in any arithmetic (2e-6 at most in
+// binary32) and of the binary32 images of w and C; 0.002 more of radius what z
+// and w are off by, and 0.1% of it the sums here.  An orbit that a cycle of period 1
+// or 2 attracts gets there unless the multiplier's modulus is close to 1.  w need not be a cycle's point: the
+// inequality alone is the proof.
+JR_HOST_DEVICE inline bool settles(float x, float y, float cr, float ci) {
+    const float eps = 2e-5f;
+    float x1 = (x * x - y * y) + cr, y1 = 2.0f * x * y + ci;
+    float x2 = (x1 * x1 - y1 * y1) + cr, y2 = 2.0f * x1 * y1 + ci;
+    const float gx = x2 - x, gy = y2 - y;
+    const float dx = 4.0f * (x * x1 - y * y1) - 1.0f, dy = 4.0f * (x * y1 + y * x1);
+    const float q = near_reciprocal(dx * dx + dy * dy);
+    const float hx = (gx * dx + gy * dy) * q, hy = (gy * dx - gx * dy) * q;
+    const float wx = x - hx, wy = y - hy;
+    x1 = (wx * wx - wy * wy) + cr;
+    y1 = 2.0f * wx * wy + ci;
+    x2 = (x1 * x1 - y1 * y1) + cr;
+    y2 = 2.0f * x1 * y1 + ci;
+    const float m0 = near_sqrt(wx * wx + wy * wy), m1 = near_sqrt(x1 * x1 + y1 * y1);
+    const float off = near_sqrt((x2 - wx) * (x2 - wx) + (y2 - wy) * (y2 - wy));
+    const float r = near_sqrt(hx * hx + hy * hy) + 0.002f;
+    const float r1 = (2.0f * m0 + r) * r + eps;
+    const float r2 = (2.0f * m1 + r1) * r1 + eps;
+    return m0 + r < 1.99f && m1 + r1 < 1.99f && off + r2 <= 0.999f * r;
+}
+
 }  // namespace jr

@@ -36,6 +36,21 @@ def test_small_images_equal_the_oracle(dtype):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["fp64", "fp32", "ff"])
+def test_single_views_of_long_bounded_orbits(dtype):
+    """Orbits that settle about cycles of period 1 and 2, or repeat, before the cap."""
+    for win, c, mode, cap in (((-2.3, 0.9, -1.2, 1.25), 0j, "mandelbrot", 700),
+                              ((-0.8, -0.7, -0.06, 0.07), 0j, "mandelbrot", 300),
+                              ((-1.3, -1.2, -0.05, 0.06), 0j, "mandelbrot", 257),
+                              ((-1.6, 1.6, -1.2, 1.2), -0.75 + 0j, "julia", 400)):
+        got = jr.render(c, win, 90, 71, cap, dtype, mode=mode)
+        torch.cuda.synchronize()
+        want = oracle.render(c, win, 90, 71, cap, dtype, mode)
+        assert (want == cap).sum() > 100
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["fp64", "fp32", "ff"])
 def test_narrow_tall_images(dtype):
     """More blocks of rows than a grid's 65535: each takes several."""
     for w, h, win in ((1, 300001, (-1.6, 1.5, -1.2, 1.25)), (17, 270003, (-1.6, 1.6, -1.2, 1.2))):

@@ -149,3 +149,51 @@ def test_a_cardioid_path_with_traps_equals_the_oracle():
         want = oracle.render(c, path.window, 160, 107, 150, "fp32")
         np.testing.assert_array_equal(v.cpu().numpy(), want, err_msg="frame %d" % k)
     plan.close()
+
+
+@pytest.fixture(scope="module")
+def settles(tmp_path_factory):
+    d = tmp_path_factory.mktemp("settles")
+    src = d / "s.cpp"
+    src.write_text('#include "julia_trap.h"\n'
+                   'extern "C" int settles(float x, float y, float a, float b) {\n'
+                   '    return jr::settles(x, y, a, b); }\n')
+    lib = str(d / "s.so")
+    subprocess.run(["g++", "-O2", "-ffp-contract=off", "-shared", "-fPIC", "-I", CSRC, str(src),
+                    "-o", lib], check=True)
+    fn = ctypes.CDLL(lib).settles
+    return lambda z, c: bool(fn(*(ctypes.c_float(v) for v in (z.real, z.imag, c.real, c.imag))))
+
+
+def test_settled_orbits_never_escape(settles):
+    """Orbits of 0 after some steps, and points up to the rims of the discs about
+    cycles of period 1 and 2, for constants in and outside the first two bulbs."""
+    rng = np.random.default_rng(3)
+    settled = tried = 0
+    for _ in range(4000):
+        c = complex(rng.uniform(-1.4, 0.5), rng.uniform(-0.8, 0.8))
+        root = cmath.sqrt(1 - 4 * c) if rng.random() < 0.6 else cmath.sqrt(-3 - 4 * c)
+        z = (1 - root) / 2 if rng.random() < 0.6 else (-1 + root) / 2
+        if rng.random() < 0.3:
+            z = 0j
+            for _ in range(int(rng.integers(0, 200))):
+                z = z * z + c if abs(z) < 2 else z
+        else:
+            a, d = rng.uniform(0, 2 * math.pi), 10 ** rng.uniform(-4, 0)
+            z += d * complex(math.cos(a), math.sin(a))
+        if not settles(z, c):
+            continue
+        settled += 1
+        for dt in ("fp32", "fp64", "ff"):
+            n = 300 if dt == "ff" else 1500
+            assert oracle.count(z, c, n, dt) == n, (z, c, dt)
+    assert settled > 300
+
+
+def test_what_does_not_settle(settles):
+    """Repelling and parabolic points, escaping orbits, NaN and infinities."""
+    for z, c in ((0j, 1j), (0.5 + 0j, 0.25 + 0j), (2 + 0j, -2 + 0j), (1.9 + 0j, 0j), (1 + 0j, 0j),
+                 (complex(math.nan, 0), 0j), (complex(math.inf, 0), 0j), (0j, complex(0, math.nan)),
+                 (complex(1e30, 1e30), 0j), (0j, 0.3 + 0.6j)):
+        assert not settles(z, c)
+    assert settles(0j, 0j) and settles(-1 + 0j, -1 + 0j) and settles(0j, -1 + 0.1j)
