@@ -2187,10 +2187,10 @@ __global__ __launch_bounds__(256) void jr_cardioid_table(CardioidArgs g) {
     DevFrame f = g.tmpl;
     f.cr = nr / a;
     f.ci = ni / a;
-    int steps;
-    if (g.traps) f.trap_p = find_trap(f.cr, f.ci, 2, &f.trap_x, &f.trap_y, &f.trap_r, &f.trap_r1,
-                                    &steps);
-    if (g.traps && f.trap_p == 0 && steps == kCriticalSteps) f.trap_p = g.tmpl.trap_p;
+    if (g.traps) {
+        const int p = find_step_trap(f.cr, f.ci, &f.trap_x, &f.trap_y, &f.trap_r, &f.trap_r1);
+        if (p > 0) f.trap_p = p;  // else as the path's other frames without one
+    }
     f.out_offset = g.out_offset0 + (int64_t)k * g.frame_px;
     f.tile_begin = (int64_t)k * g.tiles_per_frame;
     f.index = (int32_t)k;

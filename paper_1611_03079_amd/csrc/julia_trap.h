@@ -34,8 +34,7 @@ constexpr int kCriticalSteps = 512;
 // (C = -0.7279 + 0.0612i: 0.24 against 0.014), which is where orbits take
 // longest to come in.  Returns the largest radius of a falling sequence, 0 if
 // none closes above kTrapMinRadius.  `at`: the cycle's point, of `p`, to start at.
-JR_HOST_DEVICE inline double wide_radius(const double* zx, const double* zy, int p, int at, int n,
-                                         double eps) {
+inline double wide_radius(const double* zx, const double* zy, int p, int at, int n, double eps) {
     constexpr int kDegree = 16;
     double re[5][kDegree + 1] = {}, im[5][kDegree + 1] = {}, size[5][kDegree + 1];
     re[0][1] = 1.0;
@@ -70,31 +69,66 @@ JR_HOST_DEVICE inline double wide_radius(const double* zx, const double* zy, int
     return 0.0;
 }
 
-// The trap of a cycle of Z^2 + C of period 1 or 2: returns the period or 0.
-JR_HOST_DEVICE inline int find_short_trap(double cr, double ci, float* x, float* y, float* r,
-                                          float* r1) {
+// The cycle of Z^2 + C of period p = 1 or 2 in closed form, if it attracts.  `off`:
+// what p rounded steps miss its first point by.
+JR_HOST_DEVICE inline bool short_cycle(int p, double cr, double ci, double* zx, double* zy,
+                                       double* off) {
+    // period 1: z = (1 - sqrt(1 - 4 C)) / 2; period 2: (-1 + sqrt(-3 - 4 C)) / 2
+    const double ax = (p == 1 ? 1.0 : -3.0) - 4.0 * cr, ay = -4.0 * ci;
+    const double m = sqrt(ax * ax + ay * ay);
+    double sx = sqrt(0.5 * (m + fabs(ax)));
+    double sy = sx > 0.0 ? 0.5 * ay / sx : 0.0;
+    if (ax < 0.0) {
+        const double t = sx;
+        sx = fabs(sy);
+        sy = ay < 0.0 ? -t : t;
+    }
+    zx[0] = p == 1 ? 0.5 * (1.0 - sx) : 0.5 * (sx - 1.0);
+    zy[0] = p == 1 ? -0.5 * sy : 0.5 * sy;
+    zx[1] = zx[0] * zx[0] - zy[0] * zy[0] + cr;
+    zy[1] = 2.0 * zx[0] * zy[0] + ci;
+    double mult = 4.0 * (zx[0] * zx[0] + zy[0] * zy[0]);
+    mult = p == 1 ? mult : mult * 4.0 * (zx[1] * zx[1] + zy[1] * zy[1]);
+    const double bx = p == 1 ? zx[1] - zx[0] : zx[1] * zx[1] - zy[1] * zy[1] + cr - zx[0];
+    const double by = p == 1 ? zy[1] - zy[0] : 2.0 * zx[1] * zy[1] + ci - zy[0];
+    *off = sqrt(bx * bx + by * by);
+    return mult < 0.9999;  // |multiplier|^2
+}
+
+// The trap of a cycle of Z^2 + C of period 1 or 2 whose discs close step by step:
+// returns the period or 0.  A few hundred operations without arrays, for the frames
+// whose constants are made on the device: there the whole search (find_trap) held
+// 2.2 KB of stack memory a lane, and every launch of a path waited for it, 16 frames
+// of 200x150 in FP32, cap 100, with C by the cardioid's rim 386 us for now 23.
+JR_HOST_DEVICE inline int find_step_trap(double cr, double ci, float* x, float* y, float* r,
+                                         float* r1) {
     for (int p = 1; p <= 2; ++p) {
-        // period 1: z = (1 - sqrt(1 - 4 C)) / 2; period 2: (-1 + sqrt(-3 - 4 C)) / 2
-        const double ax = (p == 1 ? 1.0 : -3.0) - 4.0 * cr, ay = -4.0 * ci;
-        const double m = sqrt(ax * ax + ay * ay);
-        double sx = sqrt(0.5 * (m + fabs(ax)));
-        double sy = sx > 0.0 ? 0.5 * ay / sx : 0.0;
-        if (ax < 0.0) {
-            const double t = sx;
-            sx = fabs(sy);
-            sy = ay < 0.0 ? -t : t;
+        double zx[2], zy[2], off;
+        if (!short_cycle(p, cr, ci, zx, zy, &off)) continue;
+        const double eps = 2e-5 + off;
+        const double m0 = sqrt(zx[0] * zx[0] + zy[0] * zy[0]);
+        const double m1 = sqrt(zx[1] * zx[1] + zy[1] * zy[1]);
+        for (double d = 0.7; d >= kTrapMinRadius; d *= 0.85) {
+            const double d1 = (2.0 * m0 + d) * d + eps;
+            const double back = p == 1 ? d1 : (2.0 * m1 + d1) * d1 + eps;
+            if (back > d || m0 + d > 1.99) continue;
+            if (p == 2 && (m1 + d1 > 1.99 || d1 < kTrapMinRadius)) continue;
+            *x = (float)zx[0];
+            *y = (float)zy[0];
+            *r = (float)d;
+            *r1 = p == 2 ? (float)(0.999 * d1) : 0.0f;
+            return p;
         }
-        double zx[2], zy[2];
-        zx[0] = p == 1 ? 0.5 * (1.0 - sx) : 0.5 * (sx - 1.0);
-        zy[0] = p == 1 ? -0.5 * sy : 0.5 * sy;
-        zx[1] = zx[0] * zx[0] - zy[0] * zy[0] + cr;
-        zy[1] = 2.0 * zx[0] * zy[0] + ci;
-        double mult = 4.0 * (zx[0] * zx[0] + zy[0] * zy[0]);
-        mult = p == 1 ? mult : mult * 4.0 * (zx[1] * zx[1] + zy[1] * zy[1]);
-        if (!(mult < 0.9999)) continue;  // |multiplier|^2
-        const double bx = p == 1 ? zx[1] - zx[0] : zx[1] * zx[1] - zy[1] * zy[1] + cr - zx[0];
-        const double by = p == 1 ? zy[1] - zy[0] : 2.0 * zx[1] * zy[1] + ci - zy[0];
-        const double eps = 2e-5 + sqrt(bx * bx + by * by);
+    }
+    return 0;
+}
+
+// The same with the wider discs (wide_radius), for the host.
+inline int find_short_trap(double cr, double ci, float* x, float* y, float* r, float* r1) {
+    for (int p = 1; p <= 2; ++p) {
+        double zx[2], zy[2], off;
+        if (!short_cycle(p, cr, ci, zx, zy, &off)) continue;
+        const double eps = 2e-5 + off;
         double best[2] = {0.0, 0.0};
         for (int at = 0; at < p; ++at)
             for (int n = p; n <= 4; n += p) {
@@ -112,13 +146,13 @@ JR_HOST_DEVICE inline int find_short_trap(double cr, double ci, float* x, float*
     return 0;
 }
 
-// Iterates the critical orbit of Z^degree + C.  Returns the period of a trap
-// (its disc 0 in x, y, r; the
-// second disc's radius in r1 where the period is 2), or 0: none was found within kCriticalSteps.  `steps`
-// is the step at which the critical orbit escaped, kCriticalSteps if it did not: the higher,
-// the longer the image's orbits take.
-JR_HOST_DEVICE inline int find_trap(double cr, double ci, int degree, float* x, float* y,
-                                    float* r, float* r1, int* steps) {
+// Iterates the critical orbit of Z^degree + C, on the host.  Returns the period of a
+// trap (its disc 0 in x, y, r; the second disc's radius in r1 where the period is
+// 2), or 0: none was found within kCriticalSteps.  `steps` is the step at which the
+// critical orbit escaped, kCriticalSteps if it did not: the higher, the longer the
+// image's orbits take.
+inline int find_trap(double cr, double ci, int degree, float* x, float* y, float* r, float* r1,
+                     int* steps) {
     const double eps = 1e-5 * degree;
     double zx = 0.0, zy = 0.0, near = 0.02;
     int n = 0;
