@@ -247,11 +247,13 @@ int mandelbrot_render_plain(jr_window w, int32_t width, int32_t height,
                             void *stream);
 
 /*
- * Render n frames (any mix of sizes, caps, dtypes and modes) in ONE launch of
- * the tiled kernel (persistent work-stealing waves by default).  frames: host array of n >= 1
+ * Render n frames (any mix of sizes, caps, dtypes and modes) in ONE launch.
+ * frames: host array of n >= 1
  * descriptors, copied before return.  out_base: device arena of out_capacity
  * int32 elements holding every frame at its out_offset.  sched: NULL for the
- * default schedule of the batch's dominant dtype.  Frames must not overlap in
+ * default schedule of the batch's dominant dtype (jr_get_default_schedule; the
+ * library's own with tiles of 2 to 16 rows, the lower the fewer pixels there
+ * are in the launch).  Frames must not overlap in
  * the arena where their computed rows overlap.  A one-frame call passes the
  * frame inside the kernel arguments; without the persistent work queues it is
  * a single kernel launch that a hipGraph capture may record.  A call with
@@ -410,7 +412,9 @@ int jr_plan_info(const jr_plan *plan, int64_t *tiles, int32_t *workgroups);
 void jr_plan_destroy(jr_plan *plan);
 
 /* Library default schedule of a dtype, used by batch calls with sched NULL
- * and by one-image calls that no per-image entry covers.  There is one
+ * and by one-image calls that no per-image entry covers.  Launches too small to
+ * fill the chip with it take it with lower tiles, unless jr_set_default_schedule
+ * has given the dtype another schedule.  There is one
  * default per dtype, the same for every cap: max_iter is checked (0 ..
  * JR_MAX_ITER, JR_EINVAL otherwise) and does not change the result. */
 int jr_get_default_schedule(int32_t dtype, int32_t max_iter, jr_schedule *out);

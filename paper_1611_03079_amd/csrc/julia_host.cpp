@@ -164,19 +164,21 @@ int check_frames(const jr_frame* frames, int32_t n, int64_t capacity) {
 
 // ------------------------------------------------------------- schedules
 std::mutex g_sched_mu;
-// Defaults per dtype; the autotuner can replace them (jr_set_default_schedule).
+// Defaults per dtype, for launches that fill the chip (fit_tiles); the autotuner can
+// replace them (jr_set_default_schedule).
 // The two-phase rows kernel takes them all: it alone ends orbits in traps and
 // computes rotation-symmetric images by half.  Over an uneven batch (96 frames
 // of sides 256..4096, FP32 and float-float) it takes 1.8 ms where the tiled
 // stream took 54.8.  One wave per tile keeps one-image calls free of the work
 // queues (and so capturable).
-jr_schedule g_default[3] = {
+constexpr jr_schedule kDefault[3] = {
     // tile_w, tile_h, unroll, defer, refill, persistent, waves_per_cu, order, kernel, bail,
     // handoff
     {64, 16, 8, 0, 16, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 8, 32},   // FP64
     {64, 16, 8, 0, 16, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 16, 64},  // FP32
     {64, 16, 8, 0, 8, 0, 16, JR_ORDER_COST, JR_KERNEL_ROWS, 8, 0},     // FF
 };
+jr_schedule g_default[3] = {kDefault[0], kDefault[1], kDefault[2]};
 
 bool g_default_set[3];  // replaced by jr_set_default_schedule
 
@@ -192,6 +194,28 @@ jr_schedule default_schedule(int dtype, int32_t nframes = 0) {
     return g_default[dtype];
 }
 
+// Tiles of 64 pixels by two rows that frame f makes.
+int64_t row_pairs(const jr_frame& f) {
+    const int32_t rend = f.row_end == 0 ? f.height : f.row_end;
+    return (((int64_t)f.width + 63) / 64) * (((int64_t)rend - f.row_begin + 1) / 2);
+}
+
+// The library's own default for a launch of so many pairs of rows: the fewer there
+// are, the lower the tiles, down to two rows.  A tile is one wave's, which runs its
+// rows one after the other, so that few tall tiles leave SIMDs idle behind the
+// slowest; many low ones cost their dispatch (0.3 ns a tile).  Times for tiles of
+// 2 / 4 / 8 / 16 rows, us:
+//   one FF frame of 1024x1024 (8192 pairs)            13 / 16 / 23 / 41
+//   four FP64 Mandelbrot views of 1024x1024 (32768)  139 / 139 / 233 / 321
+//   16 FP32 frames of 1024x1024 (131072)              88 / 64 / 56 / 68
+//   64 FP64 frames of 960x540 (259200)               183 / 139 / 133 / 140
+//   64 FP32 frames of 1920x1080 (1036800)            461 / 297 / 234 / 210
+// A default that a caller has set is taken as it is.
+void fit_tiles(jr_schedule& s, int dtype, int64_t pairs) {
+    if (std::memcmp(&s, &kDefault[dtype], sizeof s) != 0) return;
+    s.tile_h = pairs < 16384 ? 2 : pairs < 65536 ? 4 : pairs < 786432 ? 8 : 16;
+}
+
 // Schedules of one-image calls by size (jr_set_image_schedule).
 struct ImageSchedule {
     int32_t dtype;
@@ -204,8 +228,9 @@ std::vector<ImageSchedule> g_image;
 
 // The entry of this dtype with the smallest cap limit covering max_iter and,
 // among those, the smallest pixel limit covering px; when no pixel limit
-// covers px, the largest one below it; otherwise the dtype's default.
-jr_schedule image_schedule(int dtype, int32_t max_iter, int64_t px) {
+// covers px, the largest one below it; otherwise the dtype's default, fitted to an
+// image of `pairs` row pairs (unless 0).
+jr_schedule image_schedule(int dtype, int32_t max_iter, int64_t px, int64_t pairs = 0) {
     std::lock_guard<std::mutex> g(g_sched_mu);
     const ImageSchedule* best = nullptr;
     for (const ImageSchedule& e : g_image) {
@@ -226,7 +251,10 @@ jr_schedule image_schedule(int dtype, int32_t max_iter, int64_t px) {
             best = &e;
         }
     }
-    return best ? best->s : g_default[dtype];
+    if (best) return best->s;
+    jr_schedule s = g_default[dtype];
+    if (pairs) fit_tiles(s, dtype, pairs);
+    return s;
 }
 
 // ------------------------------------------------------------- frame table
@@ -486,8 +514,14 @@ int batch_schedule(const jr_frame* frames, int32_t n, const jr_schedule* sched, 
         return check_schedule(s);
     }
     double w[3] = {0, 0, 0};
-    for (int32_t k = 0; k < n; ++k) w[frames[k].dtype] += frame_cost(frames[k]);
-    s = default_schedule((int)(std::max_element(w, w + 3) - w), n);
+    int64_t pairs = 0;
+    for (int32_t k = 0; k < n; ++k) {
+        w[frames[k].dtype] += frame_cost(frames[k]);
+        pairs += row_pairs(frames[k]);
+    }
+    const int dtype = (int)(std::max_element(w, w + 3) - w);
+    s = default_schedule(dtype, n);
+    fit_tiles(s, dtype, pairs);
     return JR_OK;
 }
 
@@ -791,8 +825,8 @@ int render_one(jr_complex c, jr_window w, int32_t W, int32_t H, int32_t max_iter
     int rc = check_image(W, H, max_iter, dtype, mode, c, w, who);
     if (rc) return rc;
     if ((rc = check_out(out, who))) return rc;
-    jr_schedule s = image_schedule(dtype, max_iter, (int64_t)W * H);
     jr_frame f = single_frame(c, w, W, H, max_iter, dtype, mode);
+    jr_schedule s = image_schedule(dtype, max_iter, (int64_t)W * H, row_pairs(f));
     // one image with one thread per pixel
     if (s.kernel == JR_KERNEL_PLAIN) return render_small(f, out, (hipStream_t)stream);
     return enqueue_batch(&f, 1, out, (int64_t)W * H, &s, (hipStream_t)stream);
@@ -807,7 +841,7 @@ int render_one_colored(jr_complex c, jr_window w, int32_t W, int32_t H, int32_t 
     if ((rc = check_out(out, who))) return rc;
     if ((rc = check_palette(palette, palette_len, true, who))) return rc;
     jr_frame f = single_frame(c, w, W, H, max_iter, dtype, JR_JULIA);
-    jr_schedule s = image_schedule(dtype, max_iter, (int64_t)W * H);
+    jr_schedule s = image_schedule(dtype, max_iter, (int64_t)W * H, row_pairs(f));
     if (s.kernel == JR_KERNEL_PLAIN)
         return render_small(f, reinterpret_cast<int32_t*>(out), (hipStream_t)stream, palette,
                             palette_len);
@@ -870,7 +904,11 @@ jr_schedule path_schedule(const jr_cardioid_path& p, const jr_schedule* sched, i
         *rc = check_schedule(*sched);
         return *sched;
     }
-    return default_schedule(p.dtype);
+    jr_schedule s = default_schedule(p.dtype);
+    fit_tiles(s, p.dtype,
+              p.frames * row_pairs(single_frame(jr_complex{0.0, 0.0}, p.w, p.width, p.height,
+                                                p.max_iter, p.dtype, JR_JULIA)));
+    return s;
 }
 
 // The generator's arguments (the record every frame shares; C, offset and
