@@ -375,13 +375,23 @@ int64_t tile_count(const DevFrame& d) {
     return (int64_t)d.tiles_x * ((d.row_end - d.row_begin + d.tile_h - 1) / d.tile_h);
 }
 
-// Whether the rows and single-image kernels look for the trap of a frame like f
-// (find_trap).  The search takes the host about 2 us where the critical orbit is
-// bounded (1 us where it escapes at once), which an image of fewer pixels and a
-// low cap, or of the lowest caps, does not win back.
-bool looks_for_trap(const jr_frame& f) {
-    return f.mode == JR_JULIA && f.map == JR_MAP_POLY && f.max_iter >= 32 &&
-           (f.max_iter > 128 || (int64_t)f.width * f.height >= 16384) && absorbing(f);
+// How the rows and single-image kernels look for the trap of a frame like f
+// (find_trap), one of n in a launch.  A thorough search takes the host 0.1 us where
+// the critical orbit escapes at once, 1 where it takes long and 2.5 where the cycle's
+// multiplier is close to 1, a short one at most 0.3; neither can save more than the
+// frame's iterations at the device's rate (8.9e6 of FP32's a microsecond) and its
+// share of the time in which one orbit runs to the cap.  Calls of FP32 frames, cap
+// 100, us without / by this rule / with the thorough search: 1000 of 128x128,
+// C = -0.7495: 112 / 114 / 2551; 128 of 512x512, C = -1 + 0.1i: 197 / 108 / 110.
+enum TrapSearch { kNoSearch, kShortSearch, kThoroughSearch };
+TrapSearch trap_search(const jr_frame& f, int32_t n = 1) {
+    if (f.mode != JR_JULIA || f.map != JR_MAP_POLY || f.max_iter < 32 || !absorbing(f))
+        return kNoSearch;
+    const double px = (double)f.width * f.height;
+    if (n == 1) return f.max_iter > 128 || px >= 16384.0 ? kThoroughSearch : kNoSearch;
+    const double chain = (double)f.max_iter * dtype_cost(f.dtype);
+    const double us = px * chain / 8.9e6 + 0.05 * chain / n;
+    return us < 0.5 ? kNoSearch : us < 16.0 ? kShortSearch : kThoroughSearch;
 }
 
 // Whether orbits of a frame without a trap are looked at for repeated iterates.
@@ -392,9 +402,9 @@ bool looks_for_repeats(const jr_frame& f) {
     return f.max_iter > (f.dtype == JR_FP32 ? 128 : 256);
 }
 
-// The device record of frame f (but for its first tile and its index); returns
-// its estimated cost.
-double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d) {
+// The device record of frame f, one of n (but for its first tile and its index);
+// returns its estimated cost.
+double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d, int32_t n) {
     std::memset(&d, 0, sizeof d);
     const double W = (double)f.width, H = (double)f.height;
     d.hx = (f.w.re_max - f.w.re_min) / (2.0 * W);
@@ -435,13 +445,14 @@ double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d) {
     d.tiles_x = (f.width + d.tile_w - 1) / d.tile_w;
     double steps = 256.0;
     const bool ends = s.kernel == JR_KERNEL_ROWS;
-    if (ends && looks_for_trap(f)) {
+    const TrapSearch search = ends ? trap_search(f, n) : kNoSearch;
+    if (search != kNoSearch) {
         // The critical orbit also says which of a batch's frames run long: one
         // that escapes after k steps leaves few orbits that run much longer,
         // and orbits in a trap end soon after they reach it.
         int critical;
         d.trap_p = jr::find_trap(f.c.re, f.c.im, d.degree, &d.trap_x, &d.trap_y, &d.trap_r,
-                                 &d.trap_r1, &critical);
+                                 &d.trap_r1, &critical, search == kThoroughSearch);
         steps = d.trap_p > 0 ? 16.0 : std::min(critical, 256);
         if (d.trap_p == 0 && critical == jr::kCriticalSteps && looks_for_repeats(f))
             d.trap_p = -1;
@@ -484,7 +495,7 @@ void route_rational(const jr_frame* frames, int32_t n, jr_schedule& s) {
 void build_rows(const jr_frame* frames, int32_t n, const jr_schedule& s, DevFrame* rows,
                 TableStats& t) {
     for (int32_t k = 0; k < n; ++k) {
-        const double cost = fill_frame(frames[k], s, rows[k]);
+        const double cost = fill_frame(frames[k], s, rows[k], n);
         rows[k].index = k;
         rows[k].tile_begin = (int64_t)cost;
     }
@@ -801,7 +812,7 @@ int render_small(const jr_frame& f, int32_t* out, hipStream_t stream,
     a.palette = palette;
     a.palette_len = palette_len;
     bool bounded = f.mode == JR_MANDELBROT;  // orbits without a trap may be
-    if (looks_for_trap(f)) {
+    if (trap_search(f) != kNoSearch) {
         float x, y, r, r1;
         int critical;
         const int p = jr::find_trap(f.c.re, f.c.im, 2, &x, &y, &r, &r1, &critical);
@@ -920,12 +931,12 @@ jr::CardioidArgs cardioid_args(const jr_cardioid_path& p, const jr_schedule& s, 
     jr_frame f = single_frame(jr_complex{0.0, 0.0}, p.w, p.width, p.height, p.max_iter,
                               p.dtype, JR_JULIA);
     f.out_offset = p.out_offset;
-    const double cost = fill_frame(f, s, g.tmpl);
+    const double cost = fill_frame(f, s, g.tmpl, 1);
     const int64_t tiles = tile_count(g.tmpl);
     const bool ends = s.kernel == JR_KERNEL_ROWS;
     if (g.tmpl.defer == 0) g.tmpl.defer = 1;  // every |C_k| < 1.9 (check_cardioid): escape is absorbing
     g.tmpl.trap_p = ends && looks_for_repeats(f) ? -1 : 0;  // where a bounded orbit has no trap
-    g.traps = ends && looks_for_trap(f) ? 1 : 0;
+    g.traps = ends && trap_search(f) != kNoSearch ? 1 : 0;
     g.dst = dst;
     g.step_re = p.step.re;
     g.step_im = p.step.im;

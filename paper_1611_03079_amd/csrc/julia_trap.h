@@ -24,7 +24,7 @@ namespace jr {
 // |W| < 4, one sum, C rounded to binary32); binary64 and float-float by less.
 constexpr int kTrapPeriodMax = 16;
 constexpr double kTrapMinRadius = 0.004;
-constexpr int kCriticalSteps = 512;
+constexpr int kCriticalSteps = 512, kCriticalShort = 32;
 
 // A wider disc for cycles of Z^2 + C of period 1 or 2, whose points have closed
 // forms.  About the cycle the map is h -> 2 z_k h + h^2; n steps of it are a
@@ -150,9 +150,9 @@ inline int find_short_trap(double cr, double ci, float* x, float* y, float* r, f
 // trap (its disc 0 in x, y, r; the second disc's radius in r1 where the period is
 // 2), or 0: none was found within kCriticalSteps.  `steps` is the step at which the
 // critical orbit escaped, kCriticalSteps if it did not: the higher, the longer the
-// image's orbits take.
+// image's orbits take.  Not `thorough`: no wide discs, and kCriticalShort steps only.
 inline int find_trap(double cr, double ci, int degree, float* x, float* y, float* r, float* r1,
-                     int* steps) {
+                     int* steps, bool thorough = true) {
     const double eps = 1e-5 * degree;
     double zx = 0.0, zy = 0.0, near = 0.02;
     int n = 0;
@@ -169,10 +169,12 @@ inline int find_trap(double cr, double ci, int degree, float* x, float* y, float
     *steps = kCriticalSteps;
     *r1 = 0.0f;
     if (degree == 2) {
-        const int p = find_short_trap(cr, ci, x, y, r, r1);
+        const int p = thorough ? find_short_trap(cr, ci, x, y, r, r1)
+                               : find_step_trap(cr, ci, x, y, r, r1);
         if (p > 0) return p;
     }
-    for (int stop = 32; stop <= kCriticalSteps; stop *= 4, near *= 0.2) {
+    const int last = thorough ? kCriticalSteps : kCriticalShort;
+    for (int stop = kCriticalShort; stop <= last; stop *= 4, near *= 0.2) {
         for (; n < stop; ++n) {
             if (!(zx * zx + zy * zy <= 4.0)) {
                 *steps = n;
