@@ -375,23 +375,25 @@ int64_t tile_count(const DevFrame& d) {
     return (int64_t)d.tiles_x * ((d.row_end - d.row_begin + d.tile_h - 1) / d.tile_h);
 }
 
-// How the rows and single-image kernels look for the trap of a frame like f
-// (find_trap), one of n in a launch.  A thorough search takes the host 0.1 us where
-// the critical orbit escapes at once, 1 where it takes long and 2.5 where the cycle's
-// multiplier is close to 1, a short one at most 0.3; neither can save more than the
-// frame's iterations at the device's rate (8.9e6 of FP32's a microsecond) and its
-// share of the time in which one orbit runs to the cap.  Calls of FP32 frames, cap
-// 100, us without / by this rule / with the thorough search: 1000 of 128x128,
-// C = -0.7495: 112 / 114 / 2551; 128 of 512x512, C = -1 + 0.1i: 197 / 108 / 110.
-enum TrapSearch { kNoSearch, kShortSearch, kThoroughSearch };
-TrapSearch trap_search(const jr_frame& f, int32_t n = 1) {
-    if (f.mode != JR_JULIA || f.map != JR_MAP_POLY || f.max_iter < 32 || !absorbing(f))
-        return kNoSearch;
+// The effort at which the rows and single-image kernels look for the trap of a frame
+// like f (find_trap), one of n in a launch; -1: they do not.  The search takes the
+// host 0.1 us where the critical orbit escapes at once, at most 0.3 at effort 0, 1 at
+// effort 1, and 2.5 for the wide discs where the cycle's multiplier is close to 1.  It
+// saves no more than the frame's iterations at the device's rate (8.9e6 of FP32's a
+// microsecond; 2.1 times as long in FP64, 7.3 in float-float, a further complex
+// product as long again) and its share of the time in which one orbit runs to the
+// cap.  Calls, us without the search / by this rule / at full effort: 1000 FP32
+// frames of 128x128, cap 100, C = -0.7495: 112 / 114 / 2551; 128 of 512x512, C = -1 +
+// 0.1i: 197 / 110 / 110; 16 cubic FP64 frames of 512x512, 4 of whose traps effort 0
+// misses: 63 with that, 44 / 44.
+int trap_effort(const jr_frame& f, int32_t n = 1) {
+    if (f.mode != JR_JULIA || f.map != JR_MAP_POLY || f.max_iter < 32 || !absorbing(f)) return -1;
     const double px = (double)f.width * f.height;
-    if (n == 1) return f.max_iter > 128 || px >= 16384.0 ? kThoroughSearch : kNoSearch;
-    const double chain = (double)f.max_iter * dtype_cost(f.dtype);
+    if (n == 1) return f.max_iter > 128 || px >= 16384.0 ? 2 : -1;
+    const double unit = f.dtype == JR_FF ? 7.3 : f.dtype == JR_FP64 ? 2.1 : 1.0;
+    const double chain = (double)f.max_iter * unit * (f.degree > 2 ? f.degree - 1 : 1);
     const double us = px * chain / 8.9e6 + 0.05 * chain / n;
-    return us < 0.5 ? kNoSearch : us < 16.0 ? kShortSearch : kThoroughSearch;
+    return us < 0.5 ? -1 : us < 5.5 ? 0 : us < 16.0 ? 1 : 2;
 }
 
 // Whether orbits of a frame without a trap are looked at for repeated iterates.
@@ -445,14 +447,14 @@ double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d, int32_t 
     d.tiles_x = (f.width + d.tile_w - 1) / d.tile_w;
     double steps = 256.0;
     const bool ends = s.kernel == JR_KERNEL_ROWS;
-    const TrapSearch search = ends ? trap_search(f, n) : kNoSearch;
-    if (search != kNoSearch) {
+    const int effort = ends ? trap_effort(f, n) : -1;
+    if (effort >= 0) {
         // The critical orbit also says which of a batch's frames run long: one
         // that escapes after k steps leaves few orbits that run much longer,
         // and orbits in a trap end soon after they reach it.
         int critical;
         d.trap_p = jr::find_trap(f.c.re, f.c.im, d.degree, &d.trap_x, &d.trap_y, &d.trap_r,
-                                 &d.trap_r1, &critical, search == kThoroughSearch);
+                                 &d.trap_r1, &critical, effort);
         steps = d.trap_p > 0 ? 16.0 : std::min(critical, 256);
         if (d.trap_p == 0 && critical == jr::kCriticalSteps && looks_for_repeats(f))
             d.trap_p = -1;
@@ -812,7 +814,7 @@ int render_small(const jr_frame& f, int32_t* out, hipStream_t stream,
     a.palette = palette;
     a.palette_len = palette_len;
     bool bounded = f.mode == JR_MANDELBROT;  // orbits without a trap may be
-    if (trap_search(f) != kNoSearch) {
+    if (trap_effort(f) >= 0) {
         float x, y, r, r1;
         int critical;
         const int p = jr::find_trap(f.c.re, f.c.im, 2, &x, &y, &r, &r1, &critical);
@@ -936,7 +938,7 @@ jr::CardioidArgs cardioid_args(const jr_cardioid_path& p, const jr_schedule& s, 
     const bool ends = s.kernel == JR_KERNEL_ROWS;
     if (g.tmpl.defer == 0) g.tmpl.defer = 1;  // every |C_k| < 1.9 (check_cardioid): escape is absorbing
     g.tmpl.trap_p = ends && looks_for_repeats(f) ? -1 : 0;  // where a bounded orbit has no trap
-    g.traps = ends && trap_search(f) != kNoSearch ? 1 : 0;
+    g.traps = ends && trap_effort(f) >= 0 ? 1 : 0;
     g.dst = dst;
     g.step_re = p.step.re;
     g.step_im = p.step.im;

@@ -150,9 +150,10 @@ inline int find_short_trap(double cr, double ci, float* x, float* y, float* r, f
 // trap (its disc 0 in x, y, r; the second disc's radius in r1 where the period is
 // 2), or 0: none was found within kCriticalSteps.  `steps` is the step at which the
 // critical orbit escaped, kCriticalSteps if it did not: the higher, the longer the
-// image's orbits take.  Not `thorough`: no wide discs, and kCriticalShort steps only.
+// image's orbits take.  `effort` 1: without the wide discs; 0: nor more than
+// kCriticalShort steps.
 inline int find_trap(double cr, double ci, int degree, float* x, float* y, float* r, float* r1,
-                     int* steps, bool thorough = true) {
+                     int* steps, int effort = 2) {
     const double eps = 1e-5 * degree;
     double zx = 0.0, zy = 0.0, near = 0.02;
     int n = 0;
@@ -169,11 +170,11 @@ inline int find_trap(double cr, double ci, int degree, float* x, float* y, float
     *steps = kCriticalSteps;
     *r1 = 0.0f;
     if (degree == 2) {
-        const int p = thorough ? find_short_trap(cr, ci, x, y, r, r1)
-                               : find_step_trap(cr, ci, x, y, r, r1);
+        const int p = effort > 1 ? find_short_trap(cr, ci, x, y, r, r1)
+                                 : find_step_trap(cr, ci, x, y, r, r1);
         if (p > 0) return p;
     }
-    const int last = thorough ? kCriticalSteps : kCriticalShort;
+    const int last = effort > 0 ? kCriticalSteps : kCriticalShort;
     for (int stop = kCriticalShort; stop <= last; stop *= 4, near *= 0.2) {
         for (; n < stop; ++n) {
             if (!(zx * zx + zy * zy <= 4.0)) {
