@@ -12,6 +12,7 @@ namespace jr {
 enum { kFP64 = 0, kFP32 = 1, kFF = 2 };
 enum { kModeJulia = 0, kModeMandelbrot = 1 };
 
+enum { kAbsorbs = 1, kUnscaled = 2 };
 enum { kMapPoly = 0, kMapRational = 1 };
 
 // One frame of the device frame table (144 bytes).  Built on the host from a
@@ -34,8 +35,9 @@ struct alignas(16) DevFrame {
     int32_t max_iter;
     int32_t dtype;           // kFP64 / kFP32 / kFF
     int32_t mode;            // kModeJulia / kModeMandelbrot
-    int32_t defer;           // 1: escape absorbing over the whole frame; 0: not known to
-                             // be; -1 (FP64, rows kernel): as 0, everywhere
+    int32_t defer;           // kAbsorbs: escape absorbing over the whole frame;
+                             // kUnscaled (FP64, rows kernel): a part is too small for
+                             // the form on twice the iterate or a shared reciprocal
     int32_t row_begin, row_end;
     int32_t tiles_x;         // tiles per tile row of this frame
     int32_t tile_w, tile_h;
@@ -111,6 +113,9 @@ constexpr int kRationalBit = 32;
 // progress: the stop flag and the per-frame done counters.  Launches without
 // progress run variants that hold no progress code at all.
 constexpr int kProgressBit = 64;
+// Rows kernels (every map and dtype, with counters) that also hold the plain form of
+// FP64 blocks, for launches with a frame that is kUnscaled.
+constexpr int kUnscaledBit = 128;
 
 struct PlainArgs {
     int32_t* out;

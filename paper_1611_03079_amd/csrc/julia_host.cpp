@@ -422,10 +422,10 @@ double fill_frame(const jr_frame& f, const jr_schedule& s, DevFrame& d, int32_t 
     d.dtype = f.dtype;
     d.mode = f.mode;
     d.degree = f.degree == 0 ? 2 : f.degree;
-    d.defer = absorbing(f) ? 1 : 0;
+    d.defer = absorbing(f) ? jr::kAbsorbs : 0;
     if (s.kernel == JR_KERNEL_ROWS && f.dtype == JR_FP64 &&
         (f.map == JR_MAP_RATIONAL || d.degree == 2) && !scales(f))
-        d.defer = -1;
+        d.defer |= jr::kUnscaled;
     d.map = f.map;
     d.lr = f.map == JR_MAP_RATIONAL ? f.lambda.re : 0.0;
     d.li = f.map == JR_MAP_RATIONAL ? f.lambda.im : 0.0;
@@ -471,6 +471,7 @@ void account(TableStats& t, const DevFrame& d, double cost) {
     t.total_cost += cost;
     t.max_tile_cost = std::max(t.max_tile_cost, cost / (double)tiles);
     t.dtmask |= 1 << d.dtype;
+    if (d.defer & jr::kUnscaled) t.dtmask |= jr::kUnscaledBit;
     if (d.degree > 2) t.dtmask |= jr::kGeneralBit;
     if (d.map == jr::kMapRational) t.dtmask |= jr::kGeneralBit | jr::kRationalBit;
 }
@@ -936,7 +937,7 @@ jr::CardioidArgs cardioid_args(const jr_cardioid_path& p, const jr_schedule& s, 
     const double cost = fill_frame(f, s, g.tmpl, 1);
     const int64_t tiles = tile_count(g.tmpl);
     const bool ends = s.kernel == JR_KERNEL_ROWS;
-    if (g.tmpl.defer == 0) g.tmpl.defer = 1;  // every |C_k| < 1.9 (check_cardioid): escape is absorbing
+    g.tmpl.defer |= jr::kAbsorbs;  // every |C_k| < 1.9 (check_cardioid)
     g.tmpl.trap_p = ends && looks_for_repeats(f) ? -1 : 0;  // where a bounded orbit has no trap
     g.traps = ends && trap_effort(f) >= 0 ? 1 : 0;
     g.dst = dst;
@@ -953,6 +954,7 @@ jr::CardioidArgs cardioid_args(const jr_cardioid_path& p, const jr_schedule& s, 
     t.total_cost = cost * (double)p.frames;
     t.max_tile_cost = cost / (double)tiles;
     t.dtmask = 1 << p.dtype;
+    if (g.tmpl.defer & jr::kUnscaled) t.dtmask |= jr::kUnscaledBit;
     return g;
 }
 

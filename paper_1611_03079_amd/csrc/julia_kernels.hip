@@ -96,8 +96,8 @@ struct ArF64 {
 // sum with Re C become one fma with it); binary64 operations are what bounds
 // FP64 launches (0.96 a cycle and CU).  Near underflow it does not hold: there a
 // scaled value keeps bits that the plain one loses.  The host therefore gives
-// this form only frames (DevFrame::defer 1) whose constants and window have no
-// part between 0 and 2^-200; then a product that underflows is added to a part of
+// this form only frames whose constants and window have no part between 0 and
+// 2^-200 (others run the plain form, kUnscaled); then a product that underflows is added to a part of
 // C that swallows it, or, where that part is 0, belongs to an orbit on an axis
 // that has shrunk by hundreds of binary orders and stays bounded.
 struct ArF64S {
@@ -423,8 +423,8 @@ struct ArOfDegree : G {
 // unless every bit of q's significand is set.  Inside the disc q = |Z|^2d is at
 // most 2^16.  A q below 2^-500 (0, the pole, and the next to it) or with all its
 // bits set is divided by plainly, and so is everything in frames with a part of C,
-// lambda or the window between 0 and 2^-200 (DevFrame::defer -1), where a numerator
-// could come near underflow.  Lanes that have escaped may get other values here,
+// lambda or the window between 0 and 2^-200 (kUnscaled), where a numerator could
+// come near underflow.  Lanes that have escaped may get other values here,
 // infinite or not numbers or as large as they are: none that the test takes for
 // inside.  32 frames of 1920x1080: 529 -> 452 us.
 __device__ __forceinline__ void quotients(double a, double b, double q, double& qa, double& qb) {
@@ -917,7 +917,7 @@ __device__ __forceinline__ void load_src(Src& s, const PersistentArgs& a, int64_
     const int col0 = tx * F.tile_w;
     const int row0 = F.row_begin + ty * F.tile_h;
     const int th = min(F.tile_h, F.row_end - row0);
-    s.variant = variant_of(F.dtype, F.defer, F.degree);
+    s.variant = variant_of(F.dtype, F.defer & kAbsorbs, F.degree);
     s.W = F.width;
     s.max_iter = F.max_iter;
     s.mode = F.mode;
@@ -2033,10 +2033,10 @@ __global__ __launch_bounds__(64 * WPB) void jr_rows(PersistentArgs a) {
     auto tile = [&](int64_t t) {
         CFrame& F = frames[frame_of_tile(frames, a.nframes, t, a.frames_per_tile)];
         const bool mandel = F.mode == kModeMandelbrot;
-        bool absorbs = F.defer > 0;
+        bool absorbs = (F.defer & kAbsorbs) != 0;
         // A Mandelbrot window that reaches beyond |C| = 1.9 (any view of the whole
         // set) has most of its tiles within.
-        if (F.defer == 0 && mandel) absorbs = tile_absorbs(F, t);
+        if (!absorbs && mandel) absorbs = tile_absorbs(F, t);
         const bool abs = absorbs;
         // The first block's length: the schedule's, rounded up to a multiple
         // of 4 (four iterations per trip), or 1 where escape may not be
@@ -2065,6 +2065,10 @@ __global__ __launch_bounds__(64 * WPB) void jr_rows(PersistentArgs a) {
         else JR_ROWS_(A_, 1, 1, 0);                 \
     } while (0)
 #define JR_ROWS(A_) JR_ROWS2(A_, A_)
+        // FP64 frames whose blocks keep the plain form have kernels of their own (in
+        // the kernels with calls it cost cubic coloured frames 25%)
+        constexpr bool kU = (DTMASK & kUnscaledBit) != 0;
+        const bool unscaled = kU && (F.defer & kUnscaled) != 0;
         // rational maps: Julia images in FP64 or FP32 (the host checks)
 #define JR_ROWS_R(S_, A_)                \
     do {                                 \
@@ -2081,7 +2085,12 @@ __global__ __launch_bounds__(64 * WPB) void jr_rows(PersistentArgs a) {
                 if (F.dtype == kFP32) JR_ROWS_R(ArF32R, ArF32R);
             }
             if constexpr (kR && k64) {
-                if (F.dtype == kFP64) JR_ROWS_R(ArF64RS, ArF64R);
+                if (F.dtype == kFP64) {
+                    if constexpr (kU) {
+                        if (unscaled) JR_ROWS_R(ArF64R, ArF64R);
+                    }
+                    if (!unscaled) JR_ROWS_R(ArF64RS, ArF64R);
+                }
             }
         } else if (kG && F.degree > 2) {
             // degree 3, the commonest, has its own tiles where they are inlined
@@ -2109,7 +2118,12 @@ __global__ __launch_bounds__(64 * WPB) void jr_rows(PersistentArgs a) {
                 if (F.dtype == kFP32) JR_ROWS(ArF32);
             }
             if constexpr (k64) {
-                if (F.dtype == kFP64) JR_ROWS2(ArF64S, ArF64);
+                if (F.dtype == kFP64) {
+                    if constexpr (kU) {
+                        if (unscaled) JR_ROWS(ArF64);
+                    }
+                    if (!unscaled) JR_ROWS2(ArF64S, ArF64);
+                }
             }
             if constexpr (kff) {
                 if (F.dtype == kFF) JR_ROWS(ArFF);
@@ -2286,6 +2300,11 @@ static TiledFn pick_rows_mask(int dtmask, bool one_wave, int defer) {
     if (defer && dtmask == (1 << kFP64))
         return one_wave ? jr_rows<K, 1 << kFP64, 1, 1> : jr_rows<K, 1 << kFP64, 4, 1>;
     constexpr int kGR = 7 | kGeneralBit | kRationalBit;
+    if (dtmask & kUnscaledBit) {
+        constexpr int kGRU = kGR | kProgressBit | kUnscaledBit;
+        if (dtmask & kColorBit) return jr_rows<K, kGRU | kColorBit, 4, 0>;
+        return one_wave ? jr_rows<K, kGRU, 1, 0> : jr_rows<K, kGRU, 4, 0>;
+    }
     if (dtmask & kProgressBit) {  // any frames, counted
         constexpr int kGRP = kGR | kProgressBit;
         if (dtmask & kColorBit) return jr_rows<K, kGRP | kColorBit, 4, 0>;
