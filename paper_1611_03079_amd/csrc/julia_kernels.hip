@@ -2319,8 +2319,14 @@ static TiledFn pick_rows_mask(int dtmask, bool one_wave, int defer) {
             return jr_rows<K, kGROnly | (1 << kFP32), 1, 0>;
         return one_wave ? jr_rows<K, kGR, 1, 0> : jr_rows<K, kGR, 4, 0>;
     }
-    if (one_wave && dtmask == ((1 << kFP32) | kColorBit))
-        return jr_rows<K, (1 << kFP32) | kColorBit, 1, 0>;
+    if (one_wave) {
+        switch (dtmask) {
+            case (1 << kFP32) | kColorBit: return jr_rows<K, (1 << kFP32) | kColorBit, 1, 0>;
+            case (1 << kFP64) | kColorBit: return jr_rows<K, (1 << kFP64) | kColorBit, 1, 0>;
+            case (1 << kFF) | kColorBit: return jr_rows<K, (1 << kFF) | kColorBit, 1, 0>;
+            default: break;
+        }
+    }
     if (one_wave && !(dtmask & kColorBit)) {
         switch (dtmask) {
             case (1 << kFP64) | kGeneralBit: return jr_rows<K, (1 << kFP64) | kGeneralBit, 1, 0>;
@@ -2344,6 +2350,8 @@ static TiledFn pick_rows_mask(int dtmask, bool one_wave, int defer) {
         case 1 << kFP64: return jr_rows<K, 1 << kFP64, 4, 0>;
         case 1 << kFF: return jr_rows<K, 1 << kFF, 4, 0>;
         case (1 << kFP32) | kColorBit: return jr_rows<K, (1 << kFP32) | kColorBit, 4, 0>;
+        case (1 << kFP64) | kColorBit: return jr_rows<K, (1 << kFP64) | kColorBit, 4, 0>;
+        case (1 << kFF) | kColorBit: return jr_rows<K, (1 << kFF) | kColorBit, 4, 0>;
         default: return (dtmask & kColorBit) ? jr_rows<K, 7 | kColorBit, 4, 0> : jr_rows<K, 7, 4, 0>;
     }
 }
@@ -2398,13 +2406,19 @@ hipError_t launch_plain_batch(int dtmask, const PersistentArgs& args, hipStream_
 
 // Dispatched rows tiles (one tile per wave) run in one-wave workgroups, one
 // per tile, unless they store colours from a palette larger than
-// kOneWavePalette or of a batch that is not FP32 only (such workgroups of
-// four waves stage the palette once).
+// kOneWavePalette (kOneWavePaletteWide) or of a batch that is not of one dtype's
+// quadratic maps (such workgroups of four waves stage the palette once).
+// Four waves wait for the slowest tile, and a kernel of every dtype holds float-float's
+// registers.  Two frames of 4096x4096, cap 100, default schedule, us: 256 colours in a
+// four-wave kernel of every dtype / one-wave of one dtype: FP64 542 / 325, float-float
+// 1987 / 1139; 1024 colours in four-wave / one-wave kernels of one dtype: 505 / 361 and
+// 1797 / 1226 (but long orbits 420 / 550 and 1594 / 2057).
 static bool one_wave_launch(int dtmask, const PersistentArgs& args) {
-    if (args.palette_len > 0) dtmask |= kColorBit;
     // (the counting kernels' colour variant has four-wave workgroups)
-    const bool small_palette = dtmask == ((1 << kFP32) | kColorBit) &&
-                               args.palette_len <= kOneWavePalette && !args.done;
+    const bool one_type = dtmask == (1 << kFP32) || dtmask == (1 << kFP64) || dtmask == (1 << kFF);
+    const int most = dtmask == (1 << kFP32) ? kOneWavePalette : kOneWavePaletteWide;
+    const bool small_palette = one_type && args.palette_len <= most && !args.done;
+    if (args.palette_len > 0) dtmask |= kColorBit;
     return args.rows && !args.persistent && (!(dtmask & kColorBit) || small_palette) &&
            args.total_tiles <= 0x7fffffffLL;
 }
