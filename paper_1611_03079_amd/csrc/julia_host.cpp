@@ -180,17 +180,8 @@ constexpr jr_schedule kDefault[3] = {
 };
 jr_schedule g_default[3] = {kDefault[0], kDefault[1], kDefault[2]};
 
-bool g_default_set[3];  // replaced by jr_set_default_schedule
-
-// A batch call of one FP64 frame without a schedule keeps the tiled stream that
-// it has always run.  The serving loop's tests take such a launch (1920x1080,
-// nearly all of it bounded, cap 4000) as one that outlasts the host's work on
-// the next request, 0.34 ms: it takes 6 ms here and 0.05 ms on the rows kernel.
-constexpr jr_schedule kLoneFP64 = {16, 16, 8, 0, 16, 0, 16, JR_ORDER_COST, JR_KERNEL_TILED, 8, 0};
-
-jr_schedule default_schedule(int dtype, int32_t nframes = 0) {
+jr_schedule default_schedule(int dtype) {
     std::lock_guard<std::mutex> g(g_sched_mu);
-    if (nframes == 1 && dtype == JR_FP64 && !g_default_set[dtype]) return kLoneFP64;
     return g_default[dtype];
 }
 
@@ -534,7 +525,7 @@ int batch_schedule(const jr_frame* frames, int32_t n, const jr_schedule* sched, 
         pairs += row_pairs(frames[k]);
     }
     const int dtype = (int)(std::max_element(w, w + 3) - w);
-    s = default_schedule(dtype, n);
+    s = default_schedule(dtype);
     fit_tiles(s, dtype, pairs);
     return JR_OK;
 }
@@ -1082,7 +1073,6 @@ int jr_set_default_schedule(int32_t dtype, const jr_schedule* s) {
     if (rc) return rc;
     std::lock_guard<std::mutex> g(g_sched_mu);
     g_default[dtype] = *s;
-    g_default_set[dtype] = true;
     return JR_OK;
 }
 
