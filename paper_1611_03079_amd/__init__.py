@@ -386,6 +386,11 @@ def render(c, window, width: int, height: int, max_iter: int, dtype: str = "fp64
             schedule = Schedule(kernel="plain")
         elif schedule is None and (mode != "julia" or degree != 2 or lam is not None):
             schedule = tuned_schedule(dtype, max_iter, width * height)
+            # "plain" of a one-image entry is the single-image kernel, which this
+            # call (a batch of one) does not run: the batch kernel of that name tests
+            # every iteration to the cap
+            if schedule is not None and schedule.kernel == "plain":
+                schedule = None
         if schedule is None and mode == "julia" and degree == 2 and lam is None:
             _install_image_schedules()
             c = complex(c)

@@ -384,10 +384,13 @@ def install_image_schedules(cache: Dict[str, dict], device: str) -> int:
 
 
 def apply_cache(cache: Dict[str, dict], max_iter: int = 100, pixels: int = 1 << 24):
-    """Install cached schedules for (dtype, max_iter, pixels) as library defaults."""
+    """Install cached schedules for (dtype, max_iter, pixels) as library defaults: the
+    batch bucket's, else the one-image bucket's unless that is "plain", which for one
+    image names another kernel than in a batch."""
     for dt in ("fp64", "fp32", "ff"):
-        s = lookup(cache, dt, max_iter, pixels)
-        if s is not None:
+        e = cache.get(cache_key(device_name(), dt, max_iter, pixels, batch=True))
+        s = jr.Schedule(**e["schedule"]) if e else lookup(cache, dt, max_iter, pixels)
+        if s is not None and (e or s.kernel != "plain"):
             jr.set_default_schedule(dt, s)
 
 
