@@ -347,9 +347,18 @@ def image_schedule(dtype: str, max_iter: int, pixels: int) -> Schedule:
     return Schedule.from_c(out)
 
 
+_IMAGE_ENTRIES = {}  # (dtype, max_iter_limit, pixels_limit) -> schedule, as set here
+
+
 def set_image_schedule(dtype: str, max_iter_limit: int, pixels_limit: int, schedule: Schedule):
     _check(lib.jr_set_image_schedule(DTYPES[dtype], int(max_iter_limit), int(pixels_limit),
                                      ctypes.byref(schedule.to_c())))
+    _IMAGE_ENTRIES[dtype, int(max_iter_limit), int(pixels_limit)] = schedule
+
+
+def image_entries() -> dict:
+    """The per-size schedules that were set here and are in the library's table."""
+    return {k: s for k, s in list(_IMAGE_ENTRIES.items()) if image_schedule(*k) == s}
 
 
 def render(c, window, width: int, height: int, max_iter: int, dtype: str = "fp64",

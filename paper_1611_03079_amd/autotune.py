@@ -78,6 +78,8 @@ def cache_key(device: str, dtype: str, max_iter: int, pixels: int, batch: bool =
 # clock over back-to-back render() calls.
 WALL_PIXELS = 1 << 16
 
+MAX_IMAGE_ENTRIES = 64  # of the library's per-size table
+
 
 def time_singles(frames, schedule: jr.Schedule, reps: int = 3) -> float:
     """Sum over the frames of the time of each rendered on its own.  A single
@@ -97,11 +99,12 @@ def time_render_wall(f, schedule: jr.Schedule, reps: int = 3, calls: int = 50) -
     at the end of each run (host work, launch and kernel)."""
     import torch
     out = torch.empty((f.height, f.width), dtype=torch.int32, device="cuda")
-    plain = schedule.kernel == "plain"
+    image = _is_image(f, schedule)
 
     def one():
         jr.render(f.c, f.window, f.width, f.height, f.max_iter, f.dtype, out=out,
-                  schedule=None if plain else schedule, mode=f.mode, degree=f.degree)
+                  schedule=None if image else schedule, mode=f.mode, degree=f.degree,
+                  lam=getattr(f, "lam", None))
 
     def wall():
         one()
@@ -116,27 +119,42 @@ def time_render_wall(f, schedule: jr.Schedule, reps: int = 3, calls: int = 50) -
         times.sort()
         return times[len(times) // 2]
 
-    return _as_image(f, schedule, wall) if plain else wall()
+    return _as_image(f, schedule, wall) if image else wall()
+
+
+def _is_image(f, schedule: jr.Schedule) -> bool:
+    """Whether a one-image call of f under `schedule` takes the single-image form of
+    the plain kernel: only images of the quadratic map do."""
+    return schedule.kernel == "plain" and f.degree == 2 and getattr(f, "lam", None) is None
 
 
 def _as_image(f, schedule: jr.Schedule, timed):
-    """timed() while one-image calls of f's size run `schedule`: an entry on
-    the plain kernel takes the single-image form of it, which only they do.
-    Per-size schedules that were set before are dropped; the cached ones are
-    installed again by the next call that needs them."""
-    jr.lib.jr_clear_image_schedules()
-    jr._IMAGE_SCHEDULES_DONE = True
+    """timed() while one-image calls of f's size run `schedule`, the only calls that
+    run the single-image form of the plain kernel.  If they do not already, the
+    library's per-size table holds an entry for it meanwhile, which calls of this
+    size on other threads run too; the entries that were there come back."""
+    jr._install_image_schedules()
+    key = (f.dtype, f.max_iter, f.width * f.height)
+    if jr.image_schedule(*key).kernel == schedule.kernel:
+        return timed()
+    before = jr.image_entries()
     try:
-        jr.set_image_schedule(f.dtype, f.max_iter, f.width * f.height, schedule)
+        if len(before) >= MAX_IMAGE_ENTRIES:
+            jr.lib.jr_clear_image_schedules()
+        jr.set_image_schedule(*key, schedule)
         return timed()
     finally:
         jr.lib.jr_clear_image_schedules()
-        jr._IMAGE_SCHEDULES_DONE = False  # installed again by the next call
+        jr._IMAGE_ENTRIES.clear()
+        for k, s in before.items():
+            jr.set_image_schedule(*k, s)
 
 
 def time_render_plain(f, reps: int = 3, span_ms: float = 5.0) -> float:
     """Sustained device time (ms) per render of one frame with one thread per
     pixel, as a one-image call runs it, timed like time_plan."""
+    if not _is_image(f, jr.Schedule(kernel="plain")):
+        return time_plan([f], jr.Schedule(kernel="plain"), reps=reps, span_ms=span_ms)
     return _as_image(f, jr.Schedule(kernel="plain"), lambda: _time_render(f, reps, span_ms))
 
 

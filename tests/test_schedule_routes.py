@@ -50,3 +50,73 @@ def test_apply_cache_sets_batch_schedules(monkeypatch):
     got.clear()
     autotune.apply_cache({key("fp32", batch=True): entry(plain_batch)})  # a batch's own winner
     assert got == {"fp32": plain_batch}
+
+
+class Image:
+    c, window, width, height, max_iter, dtype = 0.1j, (-1, 1, -1, 1), 40, 30, 90, "fp64"
+    mode, degree, lam = "julia", 2, None
+
+    def __init__(self, **kw):
+        self.__dict__.update(kw)
+
+
+@pytest.fixture
+def table(monkeypatch):
+    """A per-size table with a caller's entries and nothing else."""
+    monkeypatch.setattr(jr, "_IMAGE_SCHEDULES_DONE", True)
+    monkeypatch.setattr(jr, "_IMAGE_ENTRIES", {})
+    jr.lib.jr_clear_image_schedules()
+    mine = {("fp64", 128, 5000): ROWS, ("fp64", 90, 1200): jr.Schedule(64, 4, kernel="rows"),
+            ("ff", 2 ** 31 - 1, 2 ** 63 - 1): jr.Schedule(16, 16)}
+    for k, s in mine.items():
+        jr.set_image_schedule(*k, s)
+    yield mine
+    jr.lib.jr_clear_image_schedules()
+
+
+def test_timing_a_plain_entry_leaves_the_per_size_table(table):
+    def timed():
+        assert jr.image_schedule("fp64", 90, 1200) == PLAIN
+        return 7.0
+    assert autotune._as_image(Image(), PLAIN, timed) == 7.0
+    assert jr.image_entries() == table
+    for k, s in table.items():
+        assert jr.image_schedule(*k) == s
+
+    def fails():
+        raise RuntimeError("x")
+    with pytest.raises(RuntimeError):
+        autotune._as_image(Image(), PLAIN, fails)
+    assert jr.image_entries() == table
+    # entries beyond the binding's knowledge are not brought back
+    jr.lib.jr_clear_image_schedules()
+    assert jr.image_entries() == {} and autotune._as_image(Image(), PLAIN, timed) == 7.0
+    assert jr.image_entries() == {}
+
+
+def test_timing_a_plain_entry_in_a_full_or_plain_table(table):
+    for k in range(61):
+        jr.set_image_schedule("fp32", 1000 + k, 100, ROWS)
+    full = jr.image_entries()
+    assert len(full) == 64
+
+    def timed():
+        return jr.image_schedule("fp64", 90, 1200).kernel
+    assert autotune._as_image(Image(), PLAIN, timed) == "plain"
+    assert jr.image_entries() == full
+    jr.set_image_schedule("fp64", 90, 1200, PLAIN)  # already plain: nothing is touched
+    full = jr.image_entries()
+    assert autotune._as_image(Image(), PLAIN, lambda: jr.image_entries() == full) is True
+
+
+@pytest.mark.parametrize("what", [dict(degree=3), dict(lam=0.01 + 0j)])
+def test_a_general_map_s_plain_candidate_is_the_plain_kernel(monkeypatch, what):
+    """Its one-image calls are batches of one and run what they are given."""
+    seen = []
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: None)
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda: None)
+    monkeypatch.setattr(jr, "render", lambda *a, **k: seen.append(k["schedule"]))
+    autotune.time_render_wall(Image(**what), PLAIN, reps=1, calls=1)
+    assert seen and all(s == PLAIN for s in seen)
+    monkeypatch.setattr(autotune, "time_plan", lambda fr, s, **k: s.kernel)
+    assert autotune.time_render_plain(Image(**what)) == "plain"
