@@ -430,7 +430,9 @@ int jr_set_default_schedule(int32_t dtype, const jr_schedule *sched);
  * kernel is JR_KERNEL_PLAIN runs with one thread per pixel on a 2-D grid like
  * julia_render_plain, but with tests in trips of four, half the pixels of an
  * image that equals its own 180-degree rotation, and orbits ended in traps or
- * where they repeat an iterate.  An entry with the same (dtype, max_iter_limit,
+ * where they repeat an iterate; views of part of a set from 2^19 pixels on whose
+ * orbits run long (Mandelbrot views, Julia images of constants without a trap) run
+ * the rows kernel with its default schedule.  An entry with the same (dtype, max_iter_limit,
  * pixels_limit) is replaced; at most 64 entries (JR_EINVAL beyond).  The Python
  * binding installs the autotuner's per-image winners here.
  */

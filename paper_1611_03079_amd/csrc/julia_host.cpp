@@ -779,8 +779,32 @@ jr_frame single_frame(jr_complex c, jr_window w, int32_t W, int32_t H, int32_t m
     return f;
 }
 
+// Whether a view of part of a set, in which long orbits are many and apart, takes the
+// rows kernel, whose drains pack them, and not one thread per pixel; `critical` as
+// find_trap gives it, no trap having been found.  Bounded orbits without a trap are in
+// Mandelbrot views and in Julia images whose critical orbit stays bounded (but not on
+// a repelling cycle).  Those take rows in float-float from 512K pixels on, Mandelbrot
+// views only if deep (the wide ones are light), and in the other types above cap 128,
+// Julia images from 512K pixels on; from 6M pixels on, above cap 128, all Mandelbrot
+// parts do and Julia images whose critical orbit takes 128 steps to escape.  One thread
+// per pixel / rows, us: C = -0.3905 - 0.5868i, [0.1, 0.4] x [0.09, 0.31], FP32, cap
+// 1000, 1920x1080: 303 / 215; float-float, cap 100: 261 / 227; Mandelbrot 0.1 wide, FP32,
+// cap 1000, 3840x2160: 698 / 490; C = -0.7269 + 0.1889i, that part, FP32, cap 1000,
+// 4096x4096: 576 / 412.
+bool runs_long(const jr_frame& f, int critical) {
+    const int64_t px = (int64_t)f.width * f.height;
+    if (px < 1 << 19 || !absorbing(f)) return false;
+    const bool high = f.max_iter > 128, large = px >= 6000000;
+    if (f.mode == JR_MANDELBROT)
+        return (large && high) || (f.dtype == JR_FF && f.w.re_max - f.w.re_min < 1e-3);
+    if (symmetric(f)) return false;
+    if (critical < jr::kCriticalSteps) return large && high && critical >= 128;
+    return (high || f.dtype == JR_FF) && !jr::critical_orbit_repelled(f.c.re, f.c.im);
+}
+
 // One image with one thread per pixel (jr_small), `f` checked: half the pixels
 // where the image is its own rotation, orbits ended in traps or where they repeat.
+// Where its orbits run long, on the rows kernel as the library's default has it.
 int render_small(const jr_frame& f, int32_t* out, hipStream_t stream,
                  const uint32_t* palette = nullptr, int32_t palette_len = 0) {
     int dev;
@@ -806,10 +830,10 @@ int render_small(const jr_frame& f, int32_t* out, hipStream_t stream,
     a.palette = palette;
     a.palette_len = palette_len;
     bool bounded = f.mode == JR_MANDELBROT;  // orbits without a trap may be
+    int p = 0, critical = 0;
     if (trap_effort(f) >= 0) {
         float x, y, r, r1;
-        int critical;
-        const int p = jr::find_trap(f.c.re, f.c.im, 2, &x, &y, &r, &r1, &critical);
+        p = jr::find_trap(f.c.re, f.c.im, 2, &x, &y, &r, &r1, &critical);
         if (p > 0 && p <= jr::kSmallDiscs) {
             a.ends = p;
             for (int k = 0; k < p; ++k)
@@ -817,6 +841,12 @@ int render_small(const jr_frame& f, int32_t* out, hipStream_t stream,
                               a.r2[k]);
         }
         bounded = p > 0 || critical == jr::kCriticalSteps;
+    }
+    if (p == 0 && runs_long(f, critical)) {
+        jr_schedule rows = kDefault[f.dtype];
+        fit_tiles(rows, f.dtype, row_pairs(f));
+        return enqueue_batch(&f, 1, out, (int64_t)f.width * f.height, &rows, stream, palette,
+                             palette_len);
     }
     if (a.ends == 0 && bounded && looks_for_repeats(f)) a.ends = -1;
     if (!absorbing(f)) a.ends = -2;

@@ -690,9 +690,11 @@ __device__ __forceinline__ int pixel_count(typename A::Z z, const typename A::C&
 // kernel: FP32 22 -> 14.5, FP64 41 -> 24.5, float-float 130 -> 70 us; 4096x4096:
 // FP32 41 -> 33, FP64 64 -> 47.
 template <class A, int ENDS, int COLOR>
-__global__ __launch_bounds__(64) void jr_small(SmallArgs s) {
+__global__ __launch_bounds__(256) void jr_small(SmallArgs s) {
     const PlainArgs& p = s.p;
-    const int lane = (int)threadIdx.x;
+    const int lane = (int)(threadIdx.x & 63);
+    const unsigned waves = blockDim.x >> 6;
+    const unsigned wave = blockIdx.y * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     Discs discs;
     if (ENDS == kEndsTrap) {
         discs.n = s.ends;
@@ -706,7 +708,7 @@ __global__ __launch_bounds__(64) void jr_small(SmallArgs s) {
     // threads beyond the image repeat its last column or row and its stores
     const int i = min((int)blockIdx.x * 16 + (lane & 15), p.W - 1);
     // unsigned: the step past the last of 2^31 - 1 rows does not wrap
-    for (unsigned j0 = blockIdx.y * 4; j0 < (unsigned)s.rows; j0 += gridDim.y * 4) {
+    for (unsigned j0 = wave * 4; j0 < (unsigned)s.rows; j0 += gridDim.y * waves * 4) {
         const int j = (int)min(j0 + (unsigned)(lane >> 4), (unsigned)s.rows - 1u);
         const double px = pixel_re(p.cx, p.hx, i, p.W);
         const double py = pixel_im(p.cy, p.hy, j, p.H);
@@ -2511,13 +2513,13 @@ hipError_t launch_plain(int dtype, const PlainArgs& args, hipStream_t stream) {
 }
 
 template <class A>
-static void launch_small_as(dim3 grid, const SmallArgs& a, hipStream_t stream) {
+static void launch_small_as(dim3 grid, dim3 block, const SmallArgs& a, hipStream_t stream) {
     auto go = [&](auto ends) {
         constexpr int E = decltype(ends)::value;
         if (a.palette_len > 0)
-            hipLaunchKernelGGL((jr_small<A, E, 1>), grid, dim3(64), 0, stream, a);
+            hipLaunchKernelGGL((jr_small<A, E, 1>), grid, block, 0, stream, a);
         else
-            hipLaunchKernelGGL((jr_small<A, E, 0>), grid, dim3(64), 0, stream, a);
+            hipLaunchKernelGGL((jr_small<A, E, 0>), grid, block, 0, stream, a);
     };
     if (a.ends > 0)
         go(std::integral_constant<int, kEndsTrap>());
@@ -2536,19 +2538,23 @@ hipError_t launch_small(int dtype, const SmallArgs& args, hipStream_t stream) {
     // start up once for them: 4096^2 at cap 100, 131072 blocks, takes 46.7 us in
     // 65536 waves and 55.2 in 131072 in FP64, 32.8 and 42.2 in FP32 (53.4 and 37.1
     // in 16384, too few to even out).  Float-float blocks are long enough: 231 us
-    // in 131072, 255 in 65536.
+    // in 131072, 255 in 65536.  From 49152 waves on a workgroup holds four: 2048^2, 65536
+    // waves, where every orbit escapes at once, 13.0 us for 17.7; below, and where
+    // orbits are long, the four wait for one another (1366x768: up to 1.3 times).
     const int64_t waves = dtype == kFF ? 131072 : 65536;
     const int64_t fit = waves / gx > 1 ? waves / gx : 1, most = fit < 65535 ? fit : 65535;
-    dim3 grid(gx, (unsigned)(rows4 < most ? rows4 : most));
+    const int64_t gy = rows4 < most ? rows4 : most;
+    const unsigned wpb = gx * gy >= 49152 ? 4 : 1;
+    dim3 grid(gx, (unsigned)((gy + wpb - 1) / wpb)), block(64 * wpb);
     switch (dtype) {
         case kFP64:
             if (args.scaled)
-                launch_small_as<ArF64S>(grid, args, stream);
+                launch_small_as<ArF64S>(grid, block, args, stream);
             else
-                launch_small_as<ArF64>(grid, args, stream);
+                launch_small_as<ArF64>(grid, block, args, stream);
             break;
-        case kFP32: launch_small_as<ArF32>(grid, args, stream); break;
-        case kFF: launch_small_as<ArFF>(grid, args, stream); break;
+        case kFP32: launch_small_as<ArF32>(grid, block, args, stream); break;
+        case kFF: launch_small_as<ArFF>(grid, block, args, stream); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -220,6 +220,27 @@ inline int find_trap(double cr, double ci, int degree, float* x, float* y, float
     return 0;
 }
 
+// Whether the critical orbit of Z^2 + C ends on a repelling cycle of a period up to
+// kTrapPeriodMax that binary64 holds exactly (C = i, -2): the set has no interior then.
+inline bool critical_orbit_repelled(double cr, double ci) {
+    double x = 0.0, y = 0.0, ux = 0.0, uy = 0.0, m2 = 1.0;
+    for (int n = 0; n < 64 + kTrapPeriodMax; ++n) {
+        if (n >= 64) {
+            if (n == 64) {
+                ux = x;
+                uy = y;
+            } else if (x == ux && y == uy) {
+                return m2 > 1.0;
+            }
+            m2 *= 4.0 * (x * x + y * y);  // |multiplier|^2
+        }
+        const double t = x * x - y * y + cr;
+        y = 2.0 * x * y + ci;
+        x = t;
+    }
+    return false;
+}
+
 // A disc of a trap as a kernel tests it (centre and squared radius), and the step
 // from (x, y, r) to the next one.  1% + 1e-5 keeps it inside the true disc
 // whatever binary32 did to the centre and to the test itself (a centre's error
