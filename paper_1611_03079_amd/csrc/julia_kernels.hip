@@ -689,12 +689,12 @@ __device__ __forceinline__ int pixel_count(typename A::Z z, const typename A::C&
 // us a call (an empty kernel takes 3.9); 2000x2000, cap 100, against the rows
 // kernel: FP32 22 -> 14.5, FP64 41 -> 24.5, float-float 130 -> 70 us; 4096x4096:
 // FP32 41 -> 33, FP64 64 -> 47.
-template <class A, int ENDS, int COLOR>
-__global__ __launch_bounds__(256) void jr_small(SmallArgs s) {
+template <class A, int ENDS, int COLOR, int WPB>
+__global__ __launch_bounds__(64 * WPB) void jr_small(SmallArgs s) {
     const PlainArgs& p = s.p;
     const int lane = (int)(threadIdx.x & 63);
-    const unsigned waves = blockDim.x >> 6;
-    const unsigned wave = blockIdx.y * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned wave =
+        blockIdx.y * WPB + (WPB > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0u);
     Discs discs;
     if (ENDS == kEndsTrap) {
         discs.n = s.ends;
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(256) void jr_small(SmallArgs s) {
     // threads beyond the image repeat its last column or row and its stores
     const int i = min((int)blockIdx.x * 16 + (lane & 15), p.W - 1);
     // unsigned: the step past the last of 2^31 - 1 rows does not wrap
-    for (unsigned j0 = wave * 4; j0 < (unsigned)s.rows; j0 += gridDim.y * waves * 4) {
+    for (unsigned j0 = wave * 4; j0 < (unsigned)s.rows; j0 += gridDim.y * (WPB * 4)) {
         const int j = (int)min(j0 + (unsigned)(lane >> 4), (unsigned)s.rows - 1u);
         const double px = pixel_re(p.cx, p.hx, i, p.W);
         const double py = pixel_im(p.cy, p.hy, j, p.H);
@@ -2512,14 +2512,14 @@ hipError_t launch_plain(int dtype, const PlainArgs& args, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <class A>
-static void launch_small_as(dim3 grid, dim3 block, const SmallArgs& a, hipStream_t stream) {
+template <class A, int WPB>
+static void launch_small_as(dim3 grid, const SmallArgs& a, hipStream_t stream) {
     auto go = [&](auto ends) {
         constexpr int E = decltype(ends)::value;
         if (a.palette_len > 0)
-            hipLaunchKernelGGL((jr_small<A, E, 1>), grid, block, 0, stream, a);
+            hipLaunchKernelGGL((jr_small<A, E, 1, WPB>), grid, dim3(64 * WPB), 0, stream, a);
         else
-            hipLaunchKernelGGL((jr_small<A, E, 0>), grid, block, 0, stream, a);
+            hipLaunchKernelGGL((jr_small<A, E, 0, WPB>), grid, dim3(64 * WPB), 0, stream, a);
     };
     if (a.ends > 0)
         go(std::integral_constant<int, kEndsTrap>());
@@ -2540,23 +2540,31 @@ hipError_t launch_small(int dtype, const SmallArgs& args, hipStream_t stream) {
     // in 16384, too few to even out).  Float-float blocks are long enough: 231 us
     // in 131072, 255 in 65536.  From 49152 waves on a workgroup holds four: 2048^2, 65536
     // waves, where every orbit escapes at once, 13.0 us for 17.7; below, and where
-    // orbits are long, the four wait for one another (1366x768: up to 1.3 times).
+    // orbits are long, the four wait for one another (1366x768: up to 1.3 times), and
+    // with both stores of a mirrored image it is a loss (4096^2 FP64 43.4 -> 44.0).
     const int64_t waves = dtype == kFF ? 131072 : 65536;
     const int64_t fit = waves / gx > 1 ? waves / gx : 1, most = fit < 65535 ? fit : 65535;
     const int64_t gy = rows4 < most ? rows4 : most;
-    const unsigned wpb = gx * gy >= 49152 ? 4 : 1;
-    dim3 grid(gx, (unsigned)((gy + wpb - 1) / wpb)), block(64 * wpb);
-    switch (dtype) {
-        case kFP64:
-            if (args.scaled)
-                launch_small_as<ArF64S>(grid, block, args, stream);
-            else
-                launch_small_as<ArF64>(grid, block, args, stream);
-            break;
-        case kFP32: launch_small_as<ArF32>(grid, block, args, stream); break;
-        case kFF: launch_small_as<ArFF>(grid, block, args, stream); break;
-        default: return hipErrorInvalidValue;
-    }
+    const bool four = gx * gy >= 49152 && !args.mirror;
+    const dim3 grid(gx, (unsigned)(four ? (gy + 3) / 4 : gy));
+    auto go = [&](auto waves) {
+        constexpr int WPB = decltype(waves)::value;
+        switch (dtype) {
+            case kFP64:
+                if (args.scaled)
+                    launch_small_as<ArF64S, WPB>(grid, args, stream);
+                else
+                    launch_small_as<ArF64, WPB>(grid, args, stream);
+                break;
+            case kFP32: launch_small_as<ArF32, WPB>(grid, args, stream); break;
+            default: launch_small_as<ArFF, WPB>(grid, args, stream); break;
+        }
+    };
+    if (dtype != kFP64 && dtype != kFP32 && dtype != kFF) return hipErrorInvalidValue;
+    if (four)
+        go(std::integral_constant<int, 4>());
+    else
+        go(std::integral_constant<int, 1>());
     return hipGetLastError();
 }
 
