@@ -26,7 +26,8 @@ keeps the fastest there.
 Results are cached in a JSON file keyed by (device, dtype, cap bucket, pixel
 bucket); ``apply_cache`` installs the cached winners as the library defaults
 (jr_set_default_schedule), which julia_render and julia_render_batch use when
-no schedule is passed.
+no schedule is passed.  An entry whose schedule was set without a search says
+"chosen": "by hand", and in "timed_on" what its time was taken on.
 """
 import json
 import math

@@ -120,3 +120,18 @@ def test_a_general_map_s_plain_candidate_is_the_plain_kernel(monkeypatch, what):
     assert seen and all(s == PLAIN for s in seen)
     monkeypatch.setattr(autotune, "time_plan", lambda fr, s, **k: s.kernel)
     assert autotune.time_render_plain(Image(**what)) == "plain"
+
+
+def test_the_shipped_cache_says_what_its_times_are():
+    """Every entry carries a measured time; one chosen by hand says so, and what the
+    time was taken on, and claims no search."""
+    import json
+    cache = json.load(open(autotune.os.path.join(autotune.os.path.dirname(autotune.__file__),
+                                                 "autotune_cache.json")))
+    entries = {k: e for k, e in cache.items() if k != "_workloads"}
+    assert len(entries) >= 54
+    for k, e in list(entries.items()) + list(cache["_workloads"].items()):
+        assert e["ms"] > 0, k
+        assert jr.check_schedule(jr.Schedule(**e["schedule"])) == jr.JR_OK
+        if e.get("chosen") == "by hand":
+            assert e["timed_on"] and "candidates" not in e, k
