@@ -397,8 +397,12 @@ def render(c, window, width: int, height: int, max_iter: int, dtype: str = "fp64
             schedule = tuned_schedule(dtype, max_iter, width * height)
             # "plain" of a one-image entry is the single-image kernel, which this
             # call (a batch of one) does not run: the batch kernel of that name tests
-            # every iteration to the cap
-            if schedule is not None and schedule.kernel == "plain":
+            # every iteration to the cap.  It is kept for large Mandelbrot images of
+            # low caps in the wide types (4096x4096, cap 100, us, it and the default:
+            # FP64 198 and 212, float-float 546 and 786; cap 1000 FP64 1457 and 696)
+            if schedule is not None and schedule.kernel == "plain" and not (
+                    mode == "mandelbrot" and degree == 2 and lam is None and dtype != "fp32"
+                    and max_iter <= 128 and width * height >= 1 << 20):
                 schedule = None
         if schedule is None and mode == "julia" and degree == 2 and lam is None:
             _install_image_schedules()

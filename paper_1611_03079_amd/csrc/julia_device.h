@@ -173,7 +173,7 @@ hipError_t launch_tiled(int unroll, int defer, int dtmask, int blocks, const Per
 // Workgroups a launch_tiled call with this many `blocks` actually launches.
 int launch_workgroups(int dtmask, const PersistentArgs& args, int blocks);
 hipError_t launch_plain(int dtype, const PlainArgs& args, hipStream_t stream);
-// One image whose escape is absorbing, one thread per pixel, tests in blocks.
+// One image of the quadratic map, one thread per pixel, tests in blocks of four.
 hipError_t launch_small(int dtype, const SmallArgs& args, hipStream_t stream);
 
 // One thread per pixel over the frame table (tiles of 16 x 16, one workgroup each).

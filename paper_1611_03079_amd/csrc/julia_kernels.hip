@@ -7,12 +7,21 @@
 //
 // The work is plain vector-ALU arithmetic (about 8 flops per pixel-iteration,
 // nothing is read from memory, 4 bytes are written per pixel), so there is no
-// matrix-core path.  Two kernel families:
+// matrix-core path.  Four kernel families:
+//
+//   jr_rows<K,M,W,D>  the batch kernel.  A wave takes a tile of rows, runs each row's
+//                     pixels a first block of iterations and then, packed from a list
+//                     in LDS, those that are still inside.
+//
+//   jr_small<A,E,C,W> single images, one thread per pixel in trips of four tests.
+//                     Both end orbits that provably stay bounded before their cap and
+//                     compute half of an image that is its own half turn.
 //
 //   jr_plain<A>       one thread per pixel on a 2-D grid, escape test on every
 //                     iteration.  The straightforward design (the paper's own
 //                     GPU version assigns one thread to each point) and the
-//                     comparator for the tuned kernel.
+//                     comparator for the tuned kernels; jr_plain_batch over a table
+//                     of frames.
 //
 //   jr_tiled<K,D,M>   waves over a table of frames.  In persistent mode each
 //                     wave claims granules of tiles from atomic counters (64

@@ -37,6 +37,22 @@ def test_coloured_batches_of_one_take_no_plain_entry(monkeypatch, tuned, want, w
     assert seen[1].kernel == "plain"  # where it is asked for
 
 
+@pytest.mark.parametrize("dtype, cap, side, kept", [
+    ("fp64", 128, 1024, True), ("ff", 100, 2000, True), ("fp32", 100, 2000, False),
+    ("fp64", 129, 2000, False), ("ff", 100, 1023, False)])
+def test_large_mandelbrot_images_of_low_caps_keep_it(monkeypatch, dtype, cap, side, kept):
+    seen = []
+    monkeypatch.setattr(jr, "tuned_schedule", lambda *a: PLAIN)
+    monkeypatch.setattr(jr, "_out_tensor", lambda out, shape: torch.zeros(shape, dtype=torch.int32))
+    monkeypatch.setattr(jr, "_stream_ptr", lambda s: ctypes.c_void_p(0))
+    monkeypatch.setattr(jr, "_palette_ptr", lambda p: (ctypes.c_void_p(4), 2))
+    monkeypatch.setattr(jr.lib, "julia_render_batch_colored",
+                        lambda *a: seen.append(a[6]) or 0)
+    for what in (dict(mode="mandelbrot"), dict(mode="mandelbrot", degree=3), dict(degree=4)):
+        jr.render(0j, (-2, 1, -1, 1), side, side, cap, dtype, palette=object(), **what)
+    assert [s is not None for s in seen] == [kept, False, False]
+
+
 def test_apply_cache_sets_batch_schedules(monkeypatch):
     monkeypatch.setattr(autotune, "device_name", lambda: "gfx950")
     got = {}
