@@ -37,11 +37,6 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK_FP32_TFLOPS = 157.3   # MI355X vector FP32: 256 CU x 2.4 GHz x 256 flop/clk
-PEAK_FP64_TFLOPS = 78.6    # MI355X vector FP64: 256 CU x 2.4 GHz x 128 flop/clk
-# FP32 without packed instructions (the build leaves them off): one FMA per
-# lane per clock, 256 CU x 64 lanes x 2 flop x 2.4 GHz
-PEAK_FP32_UNPACKED_TFLOPS = 78.6
 PEAK_HBM_GBS = 8000.0
 FLOP_PER_ITER = 8
 BYTES_PER_PIXEL = 4
@@ -387,20 +382,14 @@ def extra_legs(args, torch, jr, wl, frames, sched, ms_headline, iters):
         outs = [torch.empty((f.height, f.width), dtype=torch.int32, device="cuda") for f in fr]
         ms_dp = time_renders(jr, torch, fr, outs, 1, plain=True)
         del outs
-        # float-float counts its useful flops against the FP32 vector peak
-        # (its hardware operation count is in profiles/)
-        peak = PEAK_FP64_TFLOPS if dt == "fp64" else PEAK_FP32_TFLOPS
-        useful_tf = FLOP_PER_ITER * it_d / (kms_d * 1e-3) / 1e12
+        # (no share of the vector peak: delivered counts are not operations run,
+        # whose number is in profiles/)
         ex["parameter_path_%s" % dt] = {
             "gpixel_iter_s": round(it_d / (ms_d * 1e-3) / 1e9, 2), "ms_per_step": round(ms_d, 4),
             "kernel_ms": round(kms_d, 4), "pixel_iters": it_d,
             "plain_per_frame_ms": round(ms_dp, 4), "vs_plain": round(ms_dp / ms_d, 3),
-            "useful_flop_frac_of_peak": round(useful_tf / peak, 4), "peak_tflops": peak,
             "schedule": (dsched.__dict__ if dsched else dsrc),
             "workgroups": info_d["workgroups"]}
-        if dt == "ff":
-            ex["parameter_path_ff"]["useful_flop_frac_of_unpacked_fp32"] = round(
-                useful_tf / PEAK_FP32_UNPACKED_TFLOPS, 4)
     # Section 3's prescribed path with a growing cardioid: 256 frames of
     # 1920x1080, four trips of 64 frames while a goes from 3.9 to 3.5, FP32,
     # cap 100; the constants are generated on the device in every step (one
@@ -462,7 +451,6 @@ def extra_legs(args, torch, jr, wl, frames, sched, ms_headline, iters):
         ms_t = time_renders(jr, torch, fr, outs, reps, plain=False)
         it_s = count_sum(torch, outs)
         ms_pl = time_renders(jr, torch, fr, outs, reps, plain=True)
-        peak = PEAK_FP32_TFLOPS if dt == "fp32" else PEAK_FP64_TFLOPS
         # each image alone (seed, cap): its mean count and both rates
         per = {}
         for k, (f, o) in enumerate(zip(fr, outs)):
@@ -477,7 +465,6 @@ def extra_legs(args, torch, jr, wl, frames, sched, ms_headline, iters):
         ex["single_4096_%s" % dt] = {
             "gpixel_iter_s": round(it_s / (ms_t * 1e-3) / 1e9, 2),
             "plain_gpixel_iter_s": round(it_s / (ms_pl * 1e-3) / 1e9, 2),
-            "frac_vector_peak": round(FLOP_PER_ITER * it_s / (ms_t * 1e-3) / 1e12 / peak, 4),
             "images": len(fr), "pixel_iters": it_s, "per_image": per}
         del outs
     # 512x512 FP64: launch-bound latency, tuned and plain
@@ -590,8 +577,6 @@ def extra_legs(args, torch, jr, wl, frames, sched, ms_headline, iters):
         "gpixel_iter_s": round(it_m / (ms_m * 1e-3) / 1e9, 2), "ms": round(ms_m, 3),
         "kernel_ms": round(kms_m, 3), "plain_per_frame_ms": round(ms_mp, 3),
         "vs_plain": round(ms_mp / ms_m, 3),
-        "useful_flop_frac_of_peak": round(FLOP_PER_ITER * it_m / (kms_m * 1e-3) / 1e12
-                                          / PEAK_FP64_TFLOPS, 4),
         "schedule": (msched.__dict__ if msched else msrc), "pixel_iters": it_m}
     # serving: open-loop Poisson arrivals at the specified rates, each for
     # --serve-seconds or --serve-requests requests, whichever ends first,
@@ -765,16 +750,14 @@ def main():
                      "traffic_source": traffic_src,
                      "algorithmic_bytes_per_launch": BYTES_PER_PIXEL * pixels,
                      "kernel_ms": round(kernel_ms, 4),
-                     "alu": {"achieved": round(alu_tflops, 2), "peak": PEAK_FP32_TFLOPS,
-                             "unit": "TFLOP/s", "frac": round(alu_tflops / PEAK_FP32_TFLOPS, 4),
-                             "peak_unpacked": PEAK_FP32_UNPACKED_TFLOPS,
-                             "frac_unpacked": round(alu_tflops / PEAK_FP32_UNPACKED_TFLOPS, 4),
-                             "flops_per_launch": FLOP_PER_ITER * iters,
-                             "flops_note": "8 x the delivered counts, not operations run: a "
-                                           "frame that is its own image under the half turn "
-                                           "has half of its orbits computed and each count "
-                                           "stored twice, and an orbit known to stay bounded "
-                                           "gets its cap without running to it"},
+                     "alu": {"delivered": round(alu_tflops, 2), "unit": "TFLOP/s",
+                             "delivered_flops_per_launch": FLOP_PER_ITER * iters,
+                             "note": "8 x the delivered counts, not operations run, so no "
+                                     "share of the card's rate: a frame that is its own "
+                                     "image under the half turn has half of its orbits "
+                                     "computed and each count stored twice, and an orbit "
+                                     "known to stay bounded gets its cap without running "
+                                     "to it"},
                      "kernel": kernel_instance(sched) + " (libjulia.so)"},
     }
     if not args.no_extra:
