@@ -89,10 +89,11 @@ JR_HOST_DEVICE inline bool short_cycle(int p, double cr, double ci, double* zx, 
     zy[1] = 2.0 * zx[0] * zy[0] + ci;
     double mult = 4.0 * (zx[0] * zx[0] + zy[0] * zy[0]);
     mult = p == 1 ? mult : mult * 4.0 * (zx[1] * zx[1] + zy[1] * zy[1]);
+    if (!(mult < 0.9999)) return false;  // |multiplier|^2
     const double bx = p == 1 ? zx[1] - zx[0] : zx[1] * zx[1] - zy[1] * zy[1] + cr - zx[0];
     const double by = p == 1 ? zy[1] - zy[0] : 2.0 * zx[1] * zy[1] + ci - zy[0];
     *off = sqrt(bx * bx + by * by);
-    return mult < 0.9999;  // |multiplier|^2
+    return true;
 }
 
 // The trap of a cycle of Z^2 + C of period 1 or 2 whose discs close step by step:
